@@ -1121,6 +1121,12 @@ static DavResult davidson_impl(Ctx* c, Arena& ws, int nroots, double conv, int m
         for (int k = 0; k < nroots; ++k) prev_rn[k] = res.rn[k];
         const int acc = orthonormalise(Tn, nn, m, R);
         if (acc == 0) {
+            if (phase > 0) {
+                // every new direction lies in the subspace: the reduced-precision phase is at its noise floor
+                // (count it as stalled; the next pass restarts in the next precision)
+                std::fill(lp_stall.begin(), lp_stall.end(), 4);
+                continue;
+            }
             res.converged = false;
             break;
         }
