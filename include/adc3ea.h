@@ -281,8 +281,9 @@ int adc3_ladder_apply_static(const double* Bvv_dev, const double* Z_dev, double*
 
 /* Symmetric eigensolver of the natural-orbital and natural-auxiliary-function steps (Sec.
  * "Frozen Natural Orbitals", eq 9 and the recanonicalisation of eqs 12-13; Sec. "Natural
- * Auxiliary Functions", eq 28): FP64 cyclic Jacobi (n > 96: over blocks of 32 rows, each round's
- * block-pair sub-matrices diagonalised in LDS and their orthogonal factors applied to A and V).
+ * Auxiliary Functions", eq 28): FP64 cyclic Jacobi (n > 96: over blocks of 16 rows, each round's
+ * block-pair sub-matrices swept in LDS and their orthogonal factors applied to A and V, the
+ * eigenvalues then taken as Rayleigh quotients with the input matrix).
  * A_dev[n][n] device, row-major, read only
  * (its symmetric part (A + A^T)/2 is diagonalised); w_dev[n] receives the eigenvalues in
  * ascending order, V_dev[n][n] the eigenvectors as columns (V[i][k] = component i of vector k),

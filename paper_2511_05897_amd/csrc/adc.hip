@@ -863,8 +863,7 @@ static DavResult davidson_impl(Ctx* c, Arena& ws, int nroots, double conv, int m
             // Loewdin within the block: T' = (U w^-1/2)^T T over the kept directions
             k_dots(Tn, N, acc, Tn, N, acc, N, Gm, acc, part, s);
             k_symmetrize(Gm, acc, s);
-            eig_small(Gm, acc, ev, Y, s);
-            k_sort_eig(ev, Y, acc, 1, Gw, Gw + acc, s);
+            eig_small_sorted(Gm, acc, ev, Y, 1, s);
             std::vector<double> hq(acc);
             d2h(hq.data(), ev, acc * sizeof(double), s);
             int keep = 0;
@@ -939,8 +938,7 @@ static DavResult davidson_impl(Ctx* c, Arena& ws, int nroots, double conv, int m
         // Rayleigh-Ritz on the (incrementally kept) Gram matrix
         k_copy2d(Gm, m, Gf, mmax, m, m, 1.0, 0.0, s);
         k_symmetrize(Gm, m, s);
-        eig_small(Gm, m, ev, Y, s);
-        k_sort_eig(ev, Y, m, 0, Gw, Gw + m, s);  // ascending, deterministic signs
+        eig_small_sorted(Gm, m, ev, Y, 0, s);  // ascending, deterministic signs
         // Ritz vectors X = Y^T V, AX = Y^T S (first nroots columns of Y)
         k_copy2d(coef, nroots, Y, m, m, nroots, 1.0, 0.0, s);
         k_lincomb(Xr, N, nroots, V, N, m, coef, nroots, N, 1.0, 0.0, s);
@@ -1283,8 +1281,7 @@ static void lock_ortho(LockJob& j, double* Tn, int nn, int m) {
         }
         k_dots(Tn, N, nn, Tn, N, nn, N, j.Gm, nn, j.part, s);
         k_symmetrize(j.Gm, nn, s);
-        eig_small(j.Gm, nn, j.ev2, j.Y2, s);
-        k_sort_eig(j.ev2, j.Y2, nn, 1, j.Gw, j.Gw + nn, s);
+        eig_small_sorted(j.Gm, nn, j.ev2, j.Y2, 1, s);
         k_lowdin_masked(j.coef, j.Y2, j.ev2, nn, 1e-14, j.valid + m, s);
         k_lincomb(j.tmp, N, nn, Tn, N, nn, j.coef, nn, N, 1.0, 0.0, s);
         k_copy(Tn, j.tmp, (long long)nn * N, s);
@@ -1308,8 +1305,7 @@ static void lock_rr(LockJob& j) {
     k_copy2d(j.Gm, m, j.Gf, j.mmax, m, m, 1.0, 0.0, s);
     k_symmetrize(j.Gm, m, s);
     k_mask_gram(j.Gm, m, j.valid, j.nvalid, s);
-    eig_small(j.Gm, m, j.ev, j.Y, s);
-    k_sort_eig(j.ev, j.Y, m, 0, j.Gw, j.Gw + m, s);
+    eig_small_sorted(j.Gm, m, j.ev, j.Y, 0, s);
     k_copy2d(j.coef, nr, j.Y, m, m, nr, 1.0, 0.0, s);
     k_lincomb(j.Xr, N, nr, j.V, N, m, j.coef, nr, N, 1.0, 0.0, s);
     k_lincomb(j.AX, N, nr, j.S, N, m, j.coef, nr, N, 1.0, 0.0, s);

@@ -294,8 +294,10 @@ void k_lincomb(double* Y, long long ldy, int nq, const double* X, long long ldx,
 // ---------------------------------------------------------------------------
 // symmetric eigensolvers (Jacobi, FP64)
 // ---------------------------------------------------------------------------
-// A[n][n] (destroyed) -> w[n] ascending, V[n][n] columns eigenvectors (row-major V[i*n+k])
-void eig_small(double* A, int n, double* w, double* V, hipStream_t s);   // n <= 96, one workgroup
+// A[n][n] -> w[n], V[n][n] columns eigenvectors (row-major V[i*n+k])
+// n <= 96, one workgroup, A kept; sorted ascending (desc 0) or descending, signs as k_sort_eig
+void eig_small_sorted(const double* A, int n, double* w, double* V, int desc, hipStream_t s);
+// any n, A destroyed, pairs unsorted
 void eig_large(double* A, int n, double* w, double* V, double* scratch, hipStream_t s);
 size_t eig_large_scratch(int n);
 // nb independent matrices of order n, contiguous A[nb][n][n] (destroyed), w[nb][n], V[nb][n][n] (unsorted, as
