@@ -10,7 +10,10 @@
 // 4 X M v^3 flops in all, against 2 M v^4 for the stored matrix: the cheaper form once X < v/2,
 // and the only one once v^4 no longer fits in HBM (v = 600: 1 TB in FP64).
 //
-// FP64 and FP32 operands: one tile kernel serves both steps (16x16x4 MFMA, FP64 or FP32
+// FP64 operands where the buffer and the work allow: both steps on dfk_kernel (both operands k-major, tiles copied
+// HBM -> LDS by buffer loads, step 1 over all rows and auxiliary functions at once; the intermediate then is
+// V[(Q,c)][(m,b)] with the roles of the two virtual indices exchanged, through the symmetry of B^Q).
+// FP64 otherwise and FP32 operands: one tile kernel serves both steps (16x16x4 MFMA, FP64 or FP32
 // accumulation): 4 waves side by side over 128 columns, TM blocks of 16 rows, double-buffered
 // LDS slabs, 16-byte loads where the shape allows (scalar loads otherwise), and two levels of
 // batch offsets.  BF16 operands: both steps read their operands k-contiguous (Z transposed per row
@@ -26,6 +29,7 @@
 //   column l%16; 32x32x16 row 8(r/4) + 4(l/32) + r%4, column l%32.
 #include "internal.h"
 #include <algorithm>
+#include <cmath>
 
 namespace adc3 {
 
@@ -622,6 +626,298 @@ void dfl_gemm(int P, int out_prec, DflArgs a, int nb1, hipStream_t s, bool bt = 
 }  // namespace
 
 namespace {
+// ---------------------------------------------------------------------------
+// FP64, both operands k-major:  C(row, col) (+)= sum_k A[k][row] B[k][col]  on v_mfma_f64_16x16x4f64, the tile
+// of ladder_f64t_kernel (TM 16-row blocks x 128 columns, 4 waves side by side, 16-deep slabs copied HBM -> LDS
+// by buffer loads, two LDS buffers, two workgroups per CU) with what the assembled ladder needs besides:
+//   * B's columns and the output's rows and columns come in groups, so that step 1 runs over all (m, c) rows and
+//     all (Q, b) columns at once with no padding per product, and writes its result where step 2 reads it k-major:
+//       step 1  V[(Q,c)][(m,b)] = sum_d Zt[d][(m,c)] B^Q[d][b]        rows (m,c), columns (Q,b), K = v
+//       step 2  C_m[a][b]      += sum_(Q,c) B^Q[c][a] V[(Q,c)][(m,b)] rows a, columns (m,b), K = q v
+//   * a slab's addresses are relative to the slab (descriptors rebuilt per slab from a 64-bit base), so K is not
+//     bounded by 32-bit offsets; rows past K and columns past the ends get an offset past the descriptor and
+//     read as zero;
+//   * K split into chunks of partial sums where the tiles of step 2 do not fill the chip.
+// What bounds it: FP64 matrix cores.  At v = 450, X = 1350, 20 rows 155 ms (63.5 TFLOP/s), against
+// 266 ms on dfl_kernel (padding of every product to 128 x 128, loads through registers, 284 workgroups in step 2);
+// at v = 200, X = 128 1.6 against 4.9 ms, at v = 201, X = 64 0.94 against 2.7 ms.
+// ---------------------------------------------------------------------------
+typedef __attribute__((address_space(3))) void* dfk_lds_t;
+constexpr unsigned DFK_OOR = 0xFFFFFFF0u;
+constexpr int DFK_BK = 16;
+
+struct DfkArgs {
+    const double* A; long long lda;          // A[k][row], row < M
+    const double* B; long long ldb, bq;      // B[k][col] at k ldb + (col / bdiv) bq + col % bdiv, col < N
+    double* C; long long r1, r0, c1, cchunk; // (row / rdiv) r1 + (row % rdiv) r0 + (col / cdiv) c1 + col % cdiv
+    int bdiv, rdiv, cdiv, rmax, cmax;        // rows with row % rdiv >= rmax and columns with col % cdiv >= cmax: dropped
+    int M, N, K, Kc, nchunk, ntm, ntn, accumulate;
+};
+
+template <int TM>
+__global__ __launch_bounds__(256, 2) void dfk_kernel(DfkArgs g) {
+    constexpr int BM = 16 * TM, RA = BM + 2, RB = 128 + 2;
+    __shared__ __attribute__((aligned(16))) double As0[DFK_BK][RA], As1[DFK_BK][RA];
+    __shared__ __attribute__((aligned(16))) double Bs0[DFK_BK][RB], Bs1[DFK_BK][RB];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lr = lane & 15, lk = lane >> 4;
+    // Workgroup id H runs on XCD H % 8: each XCD takes a contiguous range of the tile order (chunks, then bands of
+    // 8 row tiles, then column tiles, row tiles of the band fastest), so that the 64 workgroups it runs together
+    // share 8 row and 8 column tiles in its L2
+    int chunk, tm, tn;
+    {
+        const unsigned total = gridDim.x, H = blockIdx.x;
+        const unsigned per = total / 8, rem = total % 8, x = H % 8, j = H / 8;
+        unsigned L = x * per + (x < rem ? x : rem) + j;
+        const unsigned tiles = (unsigned)g.ntm * g.ntn;
+        chunk = L / tiles;
+        L -= chunk * tiles;
+        const unsigned band = L / (8u * g.ntn);
+        L -= band * 8u * g.ntn;
+        const unsigned h = min(8u, (unsigned)g.ntm - 8u * band);
+        tn = L / h;
+        tm = 8 * band + L % h;
+    }
+    const int m0 = tm * BM, n0 = tn * 128;
+    const int kb = chunk * g.Kc, klen = min(g.K, kb + g.Kc) - kb;
+    // wave w copies rows 4w .. 4w+3 of both tiles; lane l the two elements at column 2l
+    const bool acol = 2 * lane < BM;
+    const int bcol = n0 + 2 * lane, q0 = n0 / g.bdiv, ql = bcol / g.bdiv;
+    const unsigned ca = m0 + 2 * lane < g.M ? (unsigned)(2 * lane * 8) : DFK_OOR;
+    const unsigned cbo = bcol < g.N ? (unsigned)(((long long)(ql - q0) * g.bq + (bcol - ql * g.bdiv)) * 8) : DFK_OOR;
+    unsigned voa[4], vob[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        voa[r] = ca == DFK_OOR ? DFK_OOR : ca + (unsigned)((4 * wave + r) * g.lda * 8);
+        vob[r] = cbo == DFK_OOR ? DFK_OOR : cbo + (unsigned)((4 * wave + r) * g.ldb * 8);
+    }
+    const double* Ab = g.A + (long long)kb * g.lda + m0;
+    const double* Bb = g.B + (long long)kb * g.ldb + (long long)q0 * g.bq;
+    auto issue = [&](double(&At)[DFK_BK][RA], double(&Bt)[DFK_BK][RB], int s) {
+        const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(Ab + (long long)s * DFK_BK * g.lda), (short)0, 0x7fffffff, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(Bb + (long long)s * DFK_BK * g.ldb), (short)0, 0x7fffffff, 0x00020000);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const bool in = s * DFK_BK + 4 * wave + r < klen;
+            if (acol)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (dfk_lds_t)&At[4 * wave + r][0], 16, in ? voa[r] : DFK_OOR,
+                                                         0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (dfk_lds_t)&Bt[4 * wave + r][0], 16, in ? vob[r] : DFK_OOR, 0, 0,
+                                                     0);
+        }
+    };
+    d4x acc[TM][2];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = d4x{0.0, 0.0, 0.0, 0.0};
+    const int cb = wave * 32;
+    // rows and columns dealt to the MFMA blocks in interleaved pairs (one 16-byte LDS read per two blocks):
+    // row block 2h+e holds rows 32h + 2t + e, column block j columns cb + 2t + j; an odd TM's last block singly
+    auto compute = [&](const double(&At)[DFK_BK][RA], const double(&Bt)[DFK_BK][RB]) {
+#pragma unroll
+        for (int kk = 0; kk < DFK_BK; kk += 4) {
+            const d2x bq = *(const d2x*)&Bt[kk + lk][cb + 2 * lr];
+#pragma unroll
+            for (int h = 0; h < TM / 2; ++h) {
+                const d2x aq = *(const d2x*)&At[kk + lk][32 * h + 2 * lr];
+                acc[2 * h][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(aq.x, bq.x, acc[2 * h][0], 0, 0, 0);
+                acc[2 * h][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(aq.x, bq.y, acc[2 * h][1], 0, 0, 0);
+                acc[2 * h + 1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(aq.y, bq.x, acc[2 * h + 1][0], 0, 0, 0);
+                acc[2 * h + 1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(aq.y, bq.y, acc[2 * h + 1][1], 0, 0, 0);
+            }
+            if constexpr (TM & 1) {
+                const double af = At[kk + lk][16 * (TM - 1) + lr];
+                acc[TM - 1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(af, bq.x, acc[TM - 1][0], 0, 0, 0);
+                acc[TM - 1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(af, bq.y, acc[TM - 1][1], 0, 0, 0);
+            }
+        }
+    };
+    auto sync = [] {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+    };
+    const int nslab = (klen + DFK_BK - 1) / DFK_BK;
+    issue(As0, Bs0, 0);
+    sync();
+    int s = 0;
+    for (; s + 1 < nslab; s += 2) {
+        issue(As1, Bs1, s + 1);
+        compute(As0, Bs0);
+        sync();
+        if (s + 2 < nslab) issue(As0, Bs0, s + 2);
+        compute(As1, Bs1);
+        sync();
+    }
+    if (s < nslab) compute(As0, Bs0);
+    double* C = g.C + (long long)chunk * g.cchunk;
+    long long co[2];
+    bool cok[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int col = n0 + cb + 2 * lr + j, cq = col / g.cdiv, cr = col - cq * g.cdiv;
+        cok[j] = col < g.N && cr < g.cmax;
+        co[j] = (long long)cq * g.c1 + cr;
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int t = lk + 4 * r;
+            const int row = m0 + ((TM & 1) && i == TM - 1 ? 16 * i + t : 32 * (i >> 1) + 2 * t + (i & 1));
+            const int rq = row / g.rdiv, rr = row - rq * g.rdiv;
+            if (row >= g.M || rr >= g.rmax) continue;
+            const long long ro = (long long)rq * g.r1 + (long long)rr * g.r0;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                if (cok[j]) {
+                    double* c = C + ro + co[j];
+                    *c = g.accumulate ? *c + acc[i][j][r] : acc[i][j][r];
+                }
+        }
+}
+
+void dfk_launch(const DfkArgs& a, int tm, hipStream_t s) {
+    const dim3 grid((unsigned)((long long)a.nchunk * a.ntm * a.ntn));
+    switch (tm) {
+        case 1: hipLaunchKernelGGL(dfk_kernel<1>, grid, dim3(256), 0, s, a); break;
+        case 2: hipLaunchKernelGGL(dfk_kernel<2>, grid, dim3(256), 0, s, a); break;
+        case 3: hipLaunchKernelGGL(dfk_kernel<3>, grid, dim3(256), 0, s, a); break;
+        case 4: hipLaunchKernelGGL(dfk_kernel<4>, grid, dim3(256), 0, s, a); break;
+        case 5: hipLaunchKernelGGL(dfk_kernel<5>, grid, dim3(256), 0, s, a); break;
+        case 6: hipLaunchKernelGGL(dfk_kernel<6>, grid, dim3(256), 0, s, a); break;
+        case 7: hipLaunchKernelGGL(dfk_kernel<7>, grid, dim3(256), 0, s, a); break;
+        default: hipLaunchKernelGGL(dfk_kernel<8>, grid, dim3(256), 0, s, a); break;
+    }
+    LAUNCHCHK();
+}
+
+// Row tiles of height 16 tm, tm 4..8: the least n (tm + 1/4) over n tiles, that is the fewest padded 16-row blocks
+// with a quarter block of loads and barriers per tile
+void dfk_rows(long long rows, int& tm, int& mt) {
+    const long long nb = (rows + 15) / 16;
+    long long best = -1;
+    for (int t = 8; t >= 4; --t) {
+        const long long n = (nb + t - 1) / t, cost = n * (4 * t + 1);
+        if (best < 0 || cost < best) { best = cost; tm = t; mt = (int)n; }
+    }
+    if (nb < 4) { tm = (int)nb; mt = 1; }
+}
+
+// Zt[d][m vp + c] = Z[m][c][d], the pad column c = v zero; and (v odd) Bp[Q][c][vp] = B[Q][c][v], pad zero
+__global__ void dfk_zt_kernel(double* Zt, const double* Z, int v, int vp, int M) {
+    __shared__ double t[32][33];
+    const int c0 = blockIdx.x * 32, d0 = blockIdx.y * 32;
+    for (long long m = blockIdx.z; m < M; m += gridDim.z) {
+        for (int r = threadIdx.y; r < 32; r += 8) {
+            const int c = c0 + r, d = d0 + threadIdx.x;
+            t[r][threadIdx.x] = (c < v && d < v) ? Z[(m * v + c) * v + d] : 0.0;
+        }
+        __syncthreads();
+        for (int r = threadIdx.y; r < 32; r += 8) {
+            const int d = d0 + r, c = c0 + threadIdx.x;
+            if (d < v && c < vp) Zt[((long long)d * M + m) * vp + c] = t[threadIdx.x][r];
+        }
+        __syncthreads();
+    }
+}
+__global__ void dfk_pad_kernel(double* Bp, const double* B, int v, int vp, long long rows) {
+    for (long long r = blockIdx.x; r < rows; r += gridDim.x)
+        for (int c = threadIdx.x; c < vp; c += blockDim.x) Bp[r * vp + c] = c < v ? B[r * v + c] : 0.0;
+}
+
+// K chunks of step 2: enough workgroups for full rounds of the chip's 512 slots (two per CU), each chunk at least
+// 256 deep, as the partial buffer allows (355 tiles in one chunk left a third of the slots empty at v = 450, 20 rows)
+int dfk_chunks(long long tiles, long long K, long long partials) {
+    int best = 1;
+    double eff = 0.0;
+    for (int c = 1; c <= 64 && c <= std::max<long long>(1, partials) && (c == 1 || K / c >= 256); ++c) {
+        const double w = (double)tiles * c, e = w / (512.0 * std::ceil(w / 512.0));
+        if (e > eff + 0.02) { eff = e; best = c; }
+    }
+    return best;
+}
+
+// The FP64 ladder on the k-major kernel; false (nothing launched) where the buffer or the 32-bit slab offsets do
+// not allow it.  Buffer: Zt, then per auxiliary function the intermediate and (v odd) the padded factor block, and
+// the partial sums of step 2.
+bool df_ladder_k(int M, int v, int X, const double* Bvv, const double* Z, double* C, bool accumulate, double* V,
+                 long long v_elems, hipStream_t s) {
+    const int vp = v + (v & 1);
+    const long long Mv = (long long)M * vp, MN = (long long)M * v * v;
+    const auto al = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+    // a slab's 16 rows below 2^31 bytes; row, column and element counts of the products below 2^31; enough work for
+    // the extra passes (Zt, partial sums) to pay: at 1.4e8 flops 206 against 303 us on the two-step tile kernel, at
+    // 7e6 108 against 75
+    if (v < 32 || Mv < 128 || 4.0 * X * M * (double)v * v * v < 5e7 || 16 * 8 * Mv >= (1LL << 31) || MN >= (1LL << 31) || !al(V) || (v == vp && !al(Bvv))) return false;
+    const long long zt = (long long)v * Mv, per = (long long)v * Mv + (v & 1 ? (long long)v * vp : 0);
+    const long long room = v_elems - zt;
+    if (room < per) return false;
+    int tm2, mt2;
+    dfk_rows(v, tm2, mt2);
+    const long long nt2 = (Mv + 127) / 128, tiles2 = mt2 * nt2;
+    // chunks of auxiliary functions as even as the buffer allows, after the partial sums' share (at most a quarter)
+    const long long part = std::min<long long>(64, room / 4 / MN);
+    // (the products' dimensions and the workgroups of a launch stay in range: at most 2^23 tiles of step 1)
+    int tm1, mt1;
+    dfk_rows(Mv, tm1, mt1);
+    const long long qmax = std::min<long long>({(long long)X, (room - part * MN) / per, (1LL << 30) / vp,
+                                                (1LL << 23) / mt1 * 128 / vp});
+    if (qmax < 1) return false;
+    const long long nq = (X + qmax - 1) / qmax, q = (X + nq - 1) / nq;
+    double* Zt = V;
+    double* Vt = Zt + (zt + 1) / 2 * 2;
+    if (zt % 2) return false;
+    double* Bp = Vt + q * v * Mv;
+    double* P = Bp + (v & 1 ? q * v * vp : 0);
+    hipLaunchKernelGGL(dfk_zt_kernel, dim3((unsigned)((vp + 31) / 32), (unsigned)((v + 31) / 32), (unsigned)std::min(M, 4096)),
+                       dim3(32, 8), 0, s, Zt, Z, v, vp, M);
+    LAUNCHCHK();
+    for (long long Q0 = 0; Q0 < X; Q0 += q) {
+        const int qn = (int)std::min<long long>(q, X - Q0);
+        const double* Bq = Bvv + Q0 * v * v;
+        if (v & 1) {
+            hipLaunchKernelGGL(dfk_pad_kernel, dim3((unsigned)std::min<long long>((long long)qn * v, 65536)), dim3(128), 0, s,
+                               Bp, Bq, v, vp, (long long)qn * v);
+            LAUNCHCHK();
+            Bq = Bp;
+        }
+        DfkArgs a{};
+        // step 1
+        a.A = Zt; a.lda = Mv;
+        a.B = Bq; a.ldb = vp; a.bdiv = vp; a.bq = (long long)v * vp;
+        a.C = Vt; a.rdiv = vp; a.r1 = vp; a.r0 = Mv; a.rmax = v;
+        a.cdiv = vp; a.c1 = (long long)v * Mv; a.cmax = vp;
+        a.M = (int)Mv; a.N = (int)((long long)qn * vp); a.K = v; a.Kc = v; a.nchunk = 1;
+        a.ntm = mt1; a.ntn = (a.N + 127) / 128;
+        a.accumulate = 0; a.cchunk = 0;
+        dfk_launch(a, tm1, s);
+        // step 2
+        const long long K = (long long)qn * v;
+        int nch = dfk_chunks(tiles2, K, part);
+        a = DfkArgs{};
+        a.A = Bq; a.lda = vp;
+        a.B = Vt; a.ldb = Mv; a.bdiv = 0x7fffffff; a.bq = 0;
+        a.rdiv = 0x7fffffff; a.r1 = 0; a.r0 = v; a.rmax = v;
+        a.cdiv = vp; a.c1 = (long long)v * v; a.cmax = v;
+        a.M = vp; a.N = (int)Mv; a.K = (int)K;
+        a.Kc = (int)(((K + nch - 1) / nch + DFK_BK - 1) / DFK_BK * DFK_BK);
+        a.nchunk = nch = (int)((K + a.Kc - 1) / a.Kc);
+        a.ntm = mt2; a.ntn = (int)nt2;
+        const int acc = (accumulate || Q0 > 0) ? 1 : 0;
+        a.C = nch > 1 ? P : C;
+        a.cchunk = nch > 1 ? MN : 0;
+        a.accumulate = nch > 1 ? 0 : acc;
+        dfk_launch(a, tm2, s);
+        if (nch > 1) splitk_reduce(P, nch, 1, (int)MN, 1.0, acc ? 1.0 : 0.0, C, MN, 1, s);
+    }
+    return true;
+}
+}  // namespace
+
+namespace {
 // upper-triangle pair index of (i, j), i <= j < o
 __device__ inline long long pair_index(int i, int j, int o) { return (long long)i * o - (long long)i * (i - 1) / 2 + (j - i); }
 
@@ -669,6 +965,7 @@ void df_ladder(int prec, int M, int v, int X, const void* Bvv, const void* Z, do
         if (!accumulate) k_fill(C, (long long)M * vv, 0.0, s);
         return;
     }
+    if (prec == 0 && df_ladder_k(M, v, X, (const double*)Bvv, (const double*)Z, C, accumulate, (double*)V, v_elems, s)) return;
     // BF16 reads both B operands as [n][k] (16-byte LDS stores): step 1 from Z transposed per row
     // (kept at the end of the buffer), step 2 from B^Q itself, which is symmetric
     const bool bt = prec == 2;
