@@ -114,7 +114,8 @@ struct Ctx {
     long long N = 0;
     Arena ws;
     double *eo = nullptr, *ev = nullptr, *Boo = nullptr, *Bov = nullptr, *Bvv = nullptr;
-    double *ovov = nullptr, *oovv = nullptr, *T = nullptr, *M11 = nullptr, *Uz = nullptr, *diag = nullptr;
+    long long ldm = 0;  // row length of P1: o v rounded up to even
+    double *T = nullptr, *M11 = nullptr, *Uz = nullptr, *diag = nullptr;
     double *Dmp2 = nullptr;
     double *u1 = nullptr;  // second-order singles [o][v]: static self-energy and spectral amplitudes
     // eigendecomposition of M11 for the block preconditioner (computed on first use)
@@ -124,7 +125,7 @@ struct Ctx {
     // block G- [sa_lm(v)]^2 (Gm points at it)
     double *G = nullptr, *Gm = nullptr;
     bool df = false;          // ladder assembled from Bvv in every application instead of stored
-    double *P1 = nullptr;     // (ij|bd) as [i][b][j][d], level 3
+    double* P1 = nullptr;     // (ij|bd) as [(i,b)][(j,d)] with rows of ldm, level 3
     double *zb = nullptr, *xb = nullptr, *xtb = nullptr, *sdb = nullptr, *sb = nullptr;
     long long sigma_count = 0;
     // reduced-precision copies (precision 1: FP32 ladder and coupling; 2: BF16 ladder, FP32 coupling)
@@ -196,12 +197,8 @@ static Ctx* build_ctx(Arena& ws, const double* eo_in, const double* ev_in, const
     k_copy(c->Bvv, Bvv_in, X * vv, s);
     const double *Boo = c->Boo, *Bov = c->Bov, *Bvv = c->Bvv, *eo = c->eo, *ev = c->ev;
 
-    c->ovov = take(ws, ov * ov);
-    ein(ws, "Qia,Qjb->iajb", 1.0, TV(Bov, {X, o, v}), TV(Bov, {X, o, v}), 0.0, c->ovov, s);
-    c->oovv = take(ws, oo * vv);
-    ein(ws, "Qij,Qab->ijab", 1.0, TV(Boo, {X, o, o}), TV(Bvv, {X, v, v}), 0.0, c->oovv, s);
+    const long long ldm = c->ldm = ov + (ov & 1);  // rows of the (occupied, virtual)-pair matrices (setup_mats.hip)
     c->T = take(ws, oo * vv);
-    k_amp_t(c->ovov, eo, ev, o, v, c->T, s);
     const double* T = c->T;
     c->M11 = take(ws, vv);
     c->m11_Q = take(ws, vv);
@@ -211,9 +208,7 @@ static Ctx* build_ctx(Arena& ws, const double* eo_in, const double* ev_in, const
     c->u1 = take(ws, ov);
     c->diag = take(ws, c->N);
     c->Uz = take(ws, v * (long long)o * vv);
-    if (level >= 3) {
-        c->P1 = take(ws, oo * vv);
-    }
+    if (level >= 3) c->P1 = take(ws, ov * ldm);
     if (prec > 0) {
         c->Uz32 = ws.take<float>((size_t)std::max<long long>(v * (long long)o * vv, 1));
         if (level >= 3) {
@@ -240,91 +235,151 @@ static Ctx* build_ctx(Arena& ws, const double* eo_in, const double* ev_in, const
     c->sig_bytes = sigma_region_bytes(c);
     c->sig_base = ws.take<char>(c->sig_bytes);
     // ---- temporaries below; G is taken only after the U_D phase has released its own, so the
-    // setup peak is G plus the larger phase rather than G plus both ----
+    // setup peak is the pair matrices plus G plus the larger phase rather than both ----
     const size_t mark0 = ws.mark();
+    // the factor with even row strides (16-byte rows for the k-major tiles): copies for odd o v and odd v
+    const long long ldv = vv + (vv & 1);
+    const double *Bove = Bov, *Bvve = Bvv;
+    auto even_factor = [&] {
+        if (ldm != ov) {
+            double* t = take(ws, X * ldm);
+            k_copy2d(t, ldm, Bov, ov, X, ov, 1.0, 0.0, s);
+            Bove = t;
+        }
+        if (ldv != vv) {
+            double* t = take(ws, X * ldv);
+            k_copy2d(t, ldv, Bvv, vv, X, vv, 1.0, 0.0, s);
+            Bvve = t;
+        }
+    };
+    double *gm = nullptr, *Tm = nullptr, *S = nullptr;  // (ia|jb), T_ij^ab, 2 T_ij^ab - T_ij^ba
+    // (formed in each phase: a small product, against keeping them below the stored ladder)
+    auto pair_mats = [&] {
+        gm = take(ws, ov * ldm);
+        Tm = take(ws, ov * ldm);
+        S = take(ws, ov * ldm);
+        gemm_km(ws, ov, ov, X, 1.0, Bove, ldm, Bove, ldm, 0.0, gm, ldm, s);
+        k_amp_mat(gm, eo, ev, o, v, ldm, Tm, c->T, s);
+        k_pair_comb(S, ldm, Tm, ldm, o, v, 2.0, -1.0, s);
+    };
+    // P_ab (+)= alpha sum_k sum_(lc) L[(ka)][(lc)] R[(lc)][(kb)], one product per k and K chunk, summed in order
+    auto trace = [&](double alpha, const double* L, const double* R, double beta, double* P) {
+        const size_t mt = ws.mark();
+        const long long tiles = ((v + 63) / 64) * (long long)((v + 63) / 64);
+        long long nk = std::max<long long>(1, std::min<long long>(ov / 96, (512 + tiles * o - 1) / (tiles * o)));
+        const long long kc = (ov + nk - 1) / nk;
+        nk = (ov + kc - 1) / kc;
+        double* part = take(ws, nk * o * vv);
+        Gemm g;
+        g.M = v; g.N = v; g.K = (int)kc; g.Klast = (int)(ov - (nk - 1) * kc);
+        g.A = L; g.sAm = ldm; g.sAk = 1; g.bA0 = kc; g.bA1 = v * ldm;
+        g.B = R; g.sBk = ldm; g.sBn = 1; g.bB0 = kc * ldm; g.bB1 = v;
+        g.C = part; g.sCm = v; g.sCn = 1; g.bC0 = vv; g.bC1 = nk * vv;
+        g.nb0 = (int)nk; g.nb1 = o;
+        gemm(g, s);
+        if (!g_dry) splitk_reduce(part, (int)(nk * o), v, v, alpha, beta, P, v, 1, s);
+        ws.release(mt);
+    };
     {
         // phase A: D^MP2, M11 through second order, U_D (first and second order) -> U_z
         GemmScratch gscr(ws, GEMM_SCRATCH);
-        double* Tt2 = take(ws, oo * vv);  // 2T - T~
-        k_comb_t(Tt2, T, oo, v, 2.0, -1.0, s);
-        // MP2 virtual density (per spin): sum_klc (2T^ce_kl - T^ec_kl) T^cd_kl
-        ein(ws, "klce,klcd->ed", 1.0, TV(Tt2, {o, o, v, v}), TV(T, {o, o, v, v}), 0.0, c->Dmp2, s);
-        // M11 through second order
+        even_factor();
+        pair_mats();
+        if (level >= 3) {
+            // (ij|ab) as P1[(ia)][(jb)]
+            const size_t m0 = ws.mark();
+            double* oovv = take(ws, oo * vv);
+            gemm_km(ws, oo, vv, X, 1.0, Boo, oo, Bvve, ldv, 0.0, oovv, vv, s);
+            k_pair_comb(c->P1, ldm, oovv, 0, o, v, 1.0, 0.0, s);
+            ws.release(m0);
+        }
         double* P = take(ws, vv);
-        ein(ws, "klac,kblc->ab", 1.0, TV(Tt2, {o, o, v, v}), TV(c->ovov, {o, v, o, v}), 0.0, P, s);
+        trace(1.0, S, gm, 0.0, P);
         k_fill(c->M11, vv, 0.0, s);
         add_sym(c->M11, P, v, -1.0, s);
         k_add_diag(c->M11, ev, v, s);
-        if (level >= 3) {
-            // permuted integrals for the particle-hole sigma terms
-            int d_oovv[4] = {o, o, v, v};
-            int p1[4] = {0, 2, 1, 3};  // [i][j][b][d] -> [i][b][j][d]
-            k_permute4(c->P1, c->oovv, d_oovv, p1, 1.0, 0.0, s);
-        }
-        double* ooov = take(ws, oo * ov);
-        ein(ws, "Qij,Qka->ijka", 1.0, TV(Boo, {X, o, o}), TV(Bov, {X, o, v}), 0.0, ooov, s);
-        // W^Q_ic = sum_kd B^Q_kd (2T-T~)_ik^cd, and the second-order singles
-        // u1_ia = [sum_Qc B^Q_ac W^Q_ic - sum_klc (2T-T~)_kl^ac (ki|lc)] / (e_i - e_a)
         double* Bw = take(ws, X * ov);
-        ein(ws, "Qkd,ikcd->Qic", 1.0, TV(Bov, {X, o, v}), TV(Tt2, {o, o, v, v}), 0.0, Bw, s);
-        ein(ws, "Qac,Qic->ia", 1.0, TV(Bvv, {X, v, v}), TV(Bw, {X, o, v}), 0.0, c->u1, s);
-        ein(ws, "klac,kilc->ia", -1.0, TV(Tt2, {o, o, v, v}), TV(ooov, {o, o, o, v}), 1.0, c->u1, s);
-        k_div_d1(c->u1, eo, ev, o, v, s);
+        {
+            const size_t m0 = ws.mark();
+            double* Tt2 = take(ws, oo * vv);  // 2T - T~ as blocks
+            k_pair_comb(Tt2, 0, T, 0, o, v, 2.0, -1.0, s);
+            // MP2 virtual density (per spin): sum_klc (2T^ce_kl - T^ec_kl) T^cd_kl
+            ein(ws, "klce,klcd->ed", 1.0, TV(Tt2, {o, o, v, v}), TV(T, {o, o, v, v}), 0.0, c->Dmp2, s);
+            // W^Q_ic = sum_kd B^Q_kd (2T-T~)_ik^cd, and the second-order singles
+            // u1_ia = [sum_Qc B^Q_ac W^Q_ic - sum_klc (2T-T~)_kl^ac (ki|lc)] / (e_i - e_a)
+            const long long ldx = X + (X & 1);
+            double* BovT = take(ws, ov * ldx);  // [(kd)][Q]
+            k_transpose(Bov, ov, X, ov, BovT, ldx, s);
+            gemm_km(ws, X, ov, ov, 1.0, BovT, ldx, S, ldm, 0.0, Bw, ov, s);
+            ein(ws, "Qac,Qic->ia", 1.0, TV(Bvv, {X, v, v}), TV(Bw, {X, o, v}), 0.0, c->u1, s);
+            double* ooov = take(ws, oo * ov);
+            ein(ws, "Qij,Qka->ijka", 1.0, TV(Boo, {X, o, o}), TV(Bov, {X, o, v}), 0.0, ooov, s);
+            ein(ws, "klac,kilc->ia", -1.0, TV(Tt2, {o, o, v, v}), TV(ooov, {o, o, o, v}), 1.0, c->u1, s);
+            k_div_d1(c->u1, eo, ev, o, v, s);
+            ws.release(m0);
+        }
         // U_D[a][b][c][i] (first order (ab|ic), second order below) and U_z[a][i][b][c] = S + sqrt3 A over
         // (b,c), in chunks of the first virtual index a when the o v^3 tensors would crowd HBM (each
         // chunk holds a few tensors of o*na*v^2 elements)
         const int na = (int)std::max<long long>(1, std::min<long long>(v, g_chunk_elems.load() / std::max<long long>(o * vv, 1)));
-        double *Bvc = nullptr, *Boc = nullptr, *ooc = nullptr;
-        if (na < v) {
-            Bvc = take(ws, (long long)X * na * v);
-            if (level >= 3) {
-                Boc = take(ws, (long long)X * o * na);
-                ooc = take(ws, oo * o * na);
-            }
-        }
         // second-order coupling term sum_kd (2T-T~)_ik^cd (kd|ab) = sum_Q B^Q_ab W^Q_ic, W^Q_ic = sum_kd B^Q_kd
         // (2T-T~)_ik^cd: folded into the first-order product as B^Q_ab (B^Q_ic + W^Q_ic)
-        const double* Bov_u = Bov;
+        const double* Bov_u = Bove;
+        long long ldu = ldm;
+        double *ooov_p = nullptr, *Tx = nullptr;
+        const double x2 = c->smx;
         if (level >= 3) {
             k_axpby(Bw, Bov, X * ov, 1.0, c->smx, s);  // B + smx W (second order scaled for sm-ADC)
             Bov_u = Bw;
+            ldu = ov;
+            Tx = take(ws, ov * ldm);
+            k_pair_comb(Tx, ldm, Tm, ldm, o, v, 0.0, 1.0, s);
+            // (il|ka) as [(k,l)][a][i]
+            ooov_p = take(ws, oo * ov);
+            const size_t m0 = ws.mark();
+            double* ooov = take(ws, oo * ov);
+            ein(ws, "Qij,Qka->ijka", 1.0, TV(Boo, {X, o, o}), TV(Bov, {X, o, v}), 0.0, ooov, s);
+            int d4[4] = {o, o, o, v}, pm[4] = {2, 1, 3, 0};
+            k_permute4(ooov_p, ooov, d4, pm, 1.0, 0.0, s);
+            ws.release(m0);
         }
-        k_fill(c->Uz, vv * ov, 0.0, s);
         for (int a0 = 0; a0 < v; a0 += na) {
             const int nc = std::min(na, v - a0);
             const size_t mchunk = ws.mark();
             const long long E = (long long)nc * v * v * o;
+            double* Uc = c->Uz + (long long)a0 * o * vv;
             // the chunk's slices of Bvv [X][a][b] and Bov [X][k][a]
-            const double* Bvv_a = Bvv;
-            if (na < v) {
-                k_copy2d(Bvc, (long long)nc * v, Bvv + (long long)a0 * v, vv, X, (long long)nc * v, 1.0, 0.0, s);
-                Bvv_a = Bvc;
-            }
-            double* Ud = take(ws, E);
-            ein(ws, "Qab,Qic->abci", 1.0, TV(Bvv_a, {X, nc, v}), TV(Bov_u, {X, o, v}), 0.0, Ud, s);
+            const double* Bvv_a = Bvve + (long long)a0 * v;
+            double* F = take(ws, E);  // (ab|ic) and the folded term, [(a,b)][(i,c)]
+            gemm_km(ws, (long long)nc * v, ov, X, 1.0, Bvv_a, ldv, Bov_u, ldu, 0.0, F, ov, s);
+            double *C1 = nullptr, *C2 = nullptr;
+            const long long ldg = (long long)nc * v + ((long long)nc * v & 1);
             if (level >= 3) {
-                TV tT(T, {o, o, v, v});
-                const double *ooov_a = ooov, *Bov_a = Bov;
-                if (na < v) {
-                    k_copy2d(ooc, nc, ooov + a0, v, oo * o, nc, 1.0, 0.0, s);
-                    k_copy2d(Boc, nc, Bov + a0, v, (long long)X * o, nc, 1.0, 0.0, s);
-                    ooov_a = ooc;
-                    Bov_a = Boc;
+                // sum_kl T^bc_kl (ak|il) straight into U_z [(a,i)][(b,c)]
+                gemm_km(ws, (long long)nc * o, vv, oo, x2, ooov_p + (long long)a0 * o, ov, T, vv, 0.0, Uc, vv, s);
+                // sum_kd T^bd_ki (ak|cd) and sum_kd T^cd_ik (ak|bd): both against (ka|cd) as [(k,d)][(a,c)]
+                double* G2 = take(ws, ov * ldg);
+                {
+                    const size_t m0 = ws.mark();
+                    double* V1 = take(ws, E);
+                    const double* Bov_a = Bove;
+                    long long ldo = ldm;
+                    if (nc < v) {
+                        ldo = (long long)o * nc;
+                        double* Boc = take(ws, (long long)X * o * nc);
+                        k_copy2d(Boc, nc, Bov + a0, v, (long long)X * o, nc, 1.0, 0.0, s);
+                        Bov_a = Boc;
+                    }
+                    gemm_km(ws, (long long)o * nc, vv, X, 1.0, Bov_a, ldo, Bvve, ldv, 0.0, V1, vv, s);
+                    k_ovvv_perm(G2, ldg, V1, o, nc, v, s);
+                    ws.release(m0);
                 }
-                // coupling, second order (scaled by smx for sm-ADC)
-                const double x2 = c->smx;
-                ein(ws, "klbc,ilka->abci", x2, tT, TV(ooov_a, {o, o, o, nc}), 1.0, Ud, s);
-                // (ka|cd) for a in the chunk: [k][a][c][d]
-                double* ovvv1 = take(ws, E);
-                ein(ws, "Qka,Qcd->kacd", 1.0, TV(Bov_a, {X, o, nc}), TV(Bvv, {X, v, v}), 0.0, ovvv1, s);
-                TV t1(ovvv1, {o, nc, v, v});
-                ein(ws, "kibd,kacd->abci", -x2, tT, t1, 1.0, Ud, s);
-                ein(ws, "ikcd,kabd->abci", -x2, tT, t1, 1.0, Ud, s);
+                C1 = take(ws, ov * ldg);
+                C2 = take(ws, ov * ldg);
+                gemm_km(ws, ov, (long long)nc * v, ov, 1.0, Tx, ldm, G2, ldg, 0.0, C1, ldg, s);
+                gemm_km(ws, ov, (long long)nc * v, ov, 1.0, Tm, ldm, G2, ldg, 0.0, C2, ldg, s);
             }
-            double* Up = take(ws, E);
-            int d[4] = {nc, v, v, o}, pm[4] = {0, 3, 1, 2};
-            k_permute4(Up, Ud, d, pm, 1.0, 0.0, s);
-            k_d_to_z_add(c->Uz + (long long)a0 * o * vv, Up, (long long)nc * o, v, s);
+            k_uz_form(Uc, F, C1, C2, ldg, x2, nc, o, v, s);
             ws.release(mchunk);
         }
     }
@@ -344,40 +399,34 @@ static Ctx* build_ctx(Arena& ws, const double* eo_in, const double* ev_in, const
         {
             // phase B: G, then everything of M11 through third order that needs it
             GemmScratch gscr(ws, GEMM_SCRATCH);
-            double* Tt2 = take(ws, oo * vv);
-            k_comb_t(Tt2, T, oo, v, 2.0, -1.0, s);
+            even_factor();
+            pair_mats();
             double* P = take(ws, vv);
-            // stored ladder: for a chunk of a, (ac|bd) = sum_Q B^Q_ac B^Q_bd as one GEMM with rows (a,c) (from a
-            // transposed copy of Bvv) and columns (b,d), b from the chunk's first a, then folded into the pair
-            // blocks G+ and G-
+            // stored ladder: for a chunk of a, (ac|bd) = sum_Q B^Q_ac B^Q_bd as one GEMM with rows (a,c) and
+            // columns (b,d), b from the chunk's first a, then folded into the pair blocks G+ and G-
             if (!c->df) {
                 const long long v3 = (long long)v * vv;
-                // chunk: at most an eighth of the stored blocks (and the chunk budget)
-                const long long budget = std::min<long long>(g_chunk_elems.load(), stored_ladder_elems(v) / 8);
-                const int na = (int)std::max<long long>(
+                // chunk: at most an eighth of the stored blocks or 128 MB, whichever is more (at v = 83 an eighth is 4 of
+                // the 83 a: 21 products of 31 us, half empty), and the chunk budget; an even number of a, so that every
+                // chunk's slice starts on a 16-byte boundary
+                const long long budget =
+                    std::min<long long>(g_chunk_elems.load(), std::max<long long>(1LL << 24, stored_ladder_elems(v) / 8));
+                int na = (int)std::max<long long>(
                     1, std::min<long long>({(long long)v, budget / std::max<long long>(v3, 1), 65535 / v}));
+                if (na > 1 && na < v) na -= na & 1;
                 const size_t mg = ws.mark();
                 double* Gf = take(ws, (long long)na * v3);
-                double* BT = take(ws, vv * X);  // [(a,c)][Q]
-                {
-                    int d4[4] = {1, X, v, v}, p4[4] = {0, 2, 3, 1};
-                    k_permute4(BT, Bvv, d4, p4, 1.0, 0.0, s);
-                }
                 for (int a0 = 0; a0 < v; a0 += na) {
                     const int nc = std::min(na, v - a0);
                     const long long ldf = (long long)(v - a0) * v;
-                    gemm_rm(nc * v, (int)ldf, X, 1.0, BT + (long long)a0 * v * X, X, false, Bvv + (long long)a0 * v, vv,
-                            false, 0.0, Gf, ldf, s);
+                    gemm_km(ws, (long long)nc * v, ldf, X, 1.0, Bvve + (long long)a0 * v, ldv, Bvve + (long long)a0 * v,
+                            ldv, 0.0, Gf, ldf, s);
                     k_sa_form(Gf, ldf, a0, nc, v, c->G, c->Gm, s);
                 }
                 k_sa_zero_pad_rows(c->G, c->Gm, v, s);
                 ws.release(mg);
             }
-            double* oooo = take(ws, oo * oo);
-            ein(ws, "Qij,Qkl->ijkl", 1.0, TV(Boo, {X, o, o}), TV(Boo, {X, o, o}), 0.0, oooo, s);
-            double* ooov = take(ws, oo * ov);
-            ein(ws, "Qij,Qka->ijka", 1.0, TV(Boo, {X, o, o}), TV(Bov, {X, o, v}), 0.0, ooov, s);
-            // second-order doubles residual Y (alpha-beta block)
+            // ladder on the amplitudes
             double* L = take(ws, oo * vv);
             if (c->df) {
                 // T^cd_ij = T^dc_ji, so L_ji = L_ij^T: only the pairs i <= j are contracted
@@ -418,24 +467,43 @@ static Ctx* build_ctx(Arena& ws, const double* eo_in, const double* ev_in, const
                 k_sa_unpack(CW, CW + np * lp, (int)np, v, Lp, vv, s);
                 k_pairs_scatter(L, Lp, o, v, s);
             }
-            double* Y = take(ws, oo * vv);
-            k_copy(Y, L, oo * vv, s);
-            TV tT(T, {o, o, v, v}), tT2(Tt2, {o, o, v, v}), tovov(c->ovov, {o, v, o, v}), toovv(c->oovv, {o, o, v, v});
-            ein(ws, "klab,kilj->ijab", 1.0, tT, TV(oooo, {o, o, o, o}), 1.0, Y, s);
-            ein(ws, "ikac,jbkc->ijab", 1.0, tT2, tovov, 1.0, Y, s);
-            ein(ws, "ikac,kjbc->ijab", -1.0, tT, toovv, 1.0, Y, s);
-            ein(ws, "kjac,kibc->ijab", -1.0, tT, toovv, 1.0, Y, s);
-            ein(ws, "ikcb,kjac->ijab", -1.0, tT, toovv, 1.0, Y, s);
-            ein(ws, "jkbc,iakc->ijab", 1.0, tT2, tovov, 1.0, Y, s);
-            ein(ws, "jkbc,kiac->ijab", -1.0, tT, toovv, 1.0, Y, s);
-            double* U2 = Y;  // in place: U2 = Y / D
-            k_div_d2(U2, eo, ev, o, v, s);
+            // The second-order doubles and the ring part of M11 run over the same two products of pair matrices
+            // (h = (ij|ab) as P1, Tx = T_ij^ba):
+            //   RB = Tm h - S g,  RC = -Tx h
+            //   Y_ij^ab = L + H - RB[(ia)][(jb)] - RB[(jb)][(ia)] + RC[(ja)][(ib)] + RC[(ib)][(ja)]
+            //   ring_ab = sum_k (-S RB + (2 Tx - Tm) RC)[(ka)][(kb)]
+            double* RB = take(ws, ov * ldm);
+            double* RC = take(ws, ov * ldm);
+            double* E = take(ws, ov * ldm);
+            k_pair_comb(E, ldm, Tm, ldm, o, v, 0.0, 1.0, s);  // Tx
+            gemm_km(ws, ov, ov, ov, 1.0, Tm, ldm, c->P1, ldm, 0.0, RB, ldm, s);
+            gemm_km(ws, ov, ov, ov, -1.0, S, ldm, gm, ldm, 1.0, RB, ldm, s);
+            gemm_km(ws, ov, ov, ov, -1.0, E, ldm, c->P1, ldm, 0.0, RC, ldm, s);
+            k_pair_comb(E, ldm, Tm, ldm, o, v, -1.0, 2.0, s);  // 2 Tx - Tm
+            trace(-1.0, S, RB, 0.0, P);
+            trace(1.0, E, RC, 1.0, P);
+            // ladder part: sum_ekl T^ae_kl (2 L^be_kl - L^eb_kl)
+            k_pair_comb(E, ldm, L, 0, o, v, 2.0, -1.0, s);
+            trace(1.0, Tm, E, 1.0, P);
+            // second-order doubles: U2 = Y / D as a matrix, and the second-order form with them
+            {
+                const size_t m0 = ws.mark();
+                double* oooo = take(ws, oo * oo);
+                ein(ws, "Qij,Qkl->ijkl", 1.0, TV(Boo, {X, o, o}), TV(Boo, {X, o, o}), 0.0, oooo, s);
+                ein(ws, "kilj,klab->ijab", 1.0, TV(oooo, {o, o, o, o}), TV(T, {o, o, v, v}), 1.0, L, s);
+                ws.release(m0);
+            }
+            k_doubles(E, L, RB, RC, eo, ev, o, v, ldm, s);
+            k_pair_comb(RB, ldm, E, ldm, o, v, 2.0, -1.0, s);
+            trace(1.0, RB, gm, 1.0, P);
+            add_sym(c->M11, P, v, -1.0, s);
+            // second-order densities (per spin) and the static self-energy  sum_pq <ap||bq> rho_pq
             const double* u1 = c->u1;  // second-order singles (formed with the coupling)
-            // second-order densities (per spin)
+            double* Tt2 = take(ws, oo * vv);
+            k_pair_comb(Tt2, 0, T, 0, o, v, 2.0, -1.0, s);
             double* roo = take(ws, oo);
-            ein(ws, "mkcd,lkcd->ml", -1.0, tT2, tT, 0.0, roo, s);
+            ein(ws, "mkcd,lkcd->ml", -1.0, TV(Tt2, {o, o, v, v}), TV(T, {o, o, v, v}), 0.0, roo, s);
             const double* rvv = c->Dmp2;
-            // static self-energy  sum_pq <ap||bq> rho_pq
             double* J = take(ws, X);
             gemm_rm(X, 1, (int)oo, 1.0, Boo, oo, false, roo, 1, false, 0.0, J, 1, s);
             gemm_rm(X, 1, (int)vv, 1.0, Bvv, vv, false, rvv, 1, false, 1.0, J, 1, s);
@@ -449,51 +517,16 @@ static Ctx* build_ctx(Arena& ws, const double* eo_in, const double* ev_in, const
             ein(ws, "Qae,Qeb->ab", -1.0, TV(Z2, {X, v, v}), TV(Bvv, {X, v, v}), 1.0, c->M11, s);
             double* Z3 = Z1;
             ein(ws, "Qbc,kc->Qkb", 1.0, TV(Bvv, {X, v, v}), TV(u1, {o, v}), 0.0, Z3, s);
-            ein(ws, "Qka,Qkb->ab", -1.0, TV(Bov, {X, o, v}), TV(Z3, {X, o, v}), 1.0, c->M11, s);
-            ein(ws, "Qkb,Qka->ab", -1.0, TV(Bov, {X, o, v}), TV(Z3, {X, o, v}), 1.0, c->M11, s);
-            // second-order form with second-order amplitudes
-            double* U2t2 = take(ws, oo * vv);
-            k_comb_t(U2t2, U2, oo, v, 2.0, -1.0, s);
-            ein(ws, "klac,kblc->ab", 1.0, TV(U2t2, {o, o, v, v}), tovov, 0.0, P, s);
-            add_sym(c->M11, P, v, -1.0, s);
-            // ladder part: - sym( sum_ekl T^ae_kl (2 L^be_kl - L^eb_kl) )
-            double* Lt2 = U2t2;
-            k_comb_t(Lt2, L, oo, v, 2.0, -1.0, s);
-            ein(ws, "klae,klbe->ab", 1.0, tT, TV(Lt2, {o, o, v, v}), 0.0, P, s);
-            add_sym(c->M11, P, v, -1.0, s);
-            // ring part
-            double* g1 = take(ws, oo * vv);   // [d][l][b][m] = (db|ml) - (dl|mb)
-            double* g2 = take(ws, oo * vv);   // [d][l][b][m] = (dl|mb)
-            double* g3 = take(ws, oo * vv);   // [d][l][b][m] = (db|ml)
-            {
-                int d_oovv[4] = {o, o, v, v}, p_oovv[4] = {2, 1, 3, 0};  // oovv[m][l][d][b] -> [d][l][b][m]
-                int d_ovov[4] = {o, v, o, v}, p_ovov[4] = {1, 0, 3, 2};  // ovov[l][d][m][b] -> [d][l][b][m]
-                k_permute4(g3, c->oovv, d_oovv, p_oovv, 1.0, 0.0, s);
-                k_permute4(g2, c->ovov, d_ovov, p_ovov, 1.0, 0.0, s);
-                k_copy(g1, g3, oo * vv, s);
-                k_axpby(g1, g2, oo * vv, -1.0, 1.0, s);
-            }
-            double* TmT = Lt2;  // T - T~
-            k_comb_t(TmT, T, oo, v, 1.0, -1.0, s);
-            TV tg1(g1, {v, o, v, o}), tg2(g2, {v, o, v, o}), tg3(g3, {v, o, v, o}), tTm(TmT, {o, o, v, v});
-            double* RA = take(ws, oo * vv);
-            double* RB = take(ws, oo * vv);
-            double* RC = take(ws, oo * vv);
-            ein(ws, "klcd,dlbm->ckbm", 1.0, tTm, tg1, 0.0, RA, s);
-            ein(ws, "klcd,dlbm->ckbm", -1.0, tT, tg2, 1.0, RA, s);
-            ein(ws, "klcd,dlbm->ckbm", 1.0, tT, tg1, 0.0, RB, s);
-            ein(ws, "klcd,dlbm->ckbm", -1.0, tTm, tg2, 1.0, RB, s);
-            ein(ws, "kldc,dlbm->ckbm", -1.0, tT, tg3, 0.0, RC, s);
-            TV tRA(RA, {v, o, v, o}), tRB(RB, {v, o, v, o}), tRC(RC, {v, o, v, o});
-            ein(ws, "kmac,ckbm->ab", 1.0, tTm, tRA, 0.0, P, s);
-            ein(ws, "mkac,ckbm->ab", -1.0, tT, tRB, 1.0, P, s);
-            ein(ws, "kmac,ckbm->ab", 1.0, tT, tRC, 1.0, P, s);
+            // sum_Qk (Bov Z3 + its transpose)
+            ein(ws, "Qka,Qkb->ab", 2.0, TV(Bov, {X, o, v}), TV(Z3, {X, o, v}), 0.0, P, s);
             add_sym(c->M11, P, v, -1.0, s);
         }
         if (M11_2) k_axpby(c->M11, M11_2, vv, 1.0 - c->smx, c->smx, s);  // M11_2 + smx (M11_3 - M11_2)
+        k_diag_adc(c->diag, c->M11, eo, ev, Bvv, c->P1, gm, ldm, o, v, X, level, s, c->smx);
         ws.release(mark1);
+    } else {
+        k_diag_adc(c->diag, c->M11, eo, ev, nullptr, nullptr, nullptr, ldm, o, v, X, level, s, c->smx);
     }
-    k_diag_adc(c->diag, c->M11, eo, ev, Bvv, c->oovv, c->ovov, o, v, X, level, s, c->smx);
     if (prec > 0) {
         k_to_lowp(c->Uz32, c->Uz, v * (long long)o * vv, 1, s);
         if (level >= 3 && c->df) {
@@ -687,12 +720,12 @@ static void sigma_pass(Ctx* c, Arena& ws, const double* rr, double* ss, int nv, 
                 // [Y2; Y3] k-major for the ladder kernel that copies both tiles into LDS, else the row-major tile
                 const long long ldy = 2LL * Mph;
                 double* Yt = take(ws, (long long)ovi * 2 * NVMAX * v);
-                const bool tk = ladder_t_supported(2 * Mph, ovi, ovi, Yt, ldy, c->P1, ovi) &&
-                                ladder_t_min_chunks(ovi, ldy, ovi) == 1;
+                const bool tk = ladder_t_supported(2 * Mph, ovi, ovi, Yt, ldy, c->P1, c->ldm) &&
+                                ladder_t_min_chunks(ovi, ldy, c->ldm) == 1;
                 if (tk) k_transpose(Y2, ovi, 2 * Mph, ovi, Yt, ldy, s);
-                const bool lad = !tk && ladder_supported(2 * Mph, ovi, ovi, Y2, ovi, c->P1, ovi, E, ovi);
-                const int nch = tk    ? ladder_tuned_chunks(3, 2 * Mph, ovi, ovi, Yt, ldy, c->P1, ovi, E, ovi, part, pe, s)
-                                : lad ? ladder_tuned_chunks(0, 2 * Mph, ovi, ovi, Y2, ovi, c->P1, ovi, E, ovi, part, pe, s)
+                const bool lad = !tk && ladder_supported(2 * Mph, ovi, ovi, Y2, ovi, c->P1, c->ldm, E, ovi);
+                const int nch = tk    ? ladder_tuned_chunks(3, 2 * Mph, ovi, ovi, Yt, ldy, c->P1, c->ldm, E, ovi, part, pe, s)
+                                : lad ? ladder_tuned_chunks(0, 2 * Mph, ovi, ovi, Y2, ovi, c->P1, c->ldm, E, ovi, part, pe, s)
                                       : 1;
                 {
                     Gemm g;  // Wq[(n,a)][Q] = sum_(j,d) Y1[(n,a)][(j,d)] Bov[Q][(j,d)]
@@ -700,17 +733,17 @@ static void sigma_pass(Ctx* c, Arena& ws, const double* rr, double* ss, int nv, 
                     g.A = Y1; g.sAm = ovi; g.sAk = 1;
                     g.B = c->Bov; g.sBk = 1; g.sBn = ovi;
                     g.C = Wq; g.sCm = X; g.sCn = 1;
-                    gemm_split(g, s);
+                    gemm(g, s);
                 }
                 gemm_rm(Mph, ovi, X, 1.0, Wq, X, false, c->Bov, ovi, false, 0.0, D, ovi, s);
                 // (a fixed chunk count may not fit the partial buffer: clamped, as the row-major path does)
                 const int ncht = (int)std::max<long long>(1, std::min<long long>(nch, pe / (2LL * Mph * ovi)));
-                if (tk && ladder_gemm_t(2 * Mph, ovi, ovi, 1.0, Yt, ldy, c->P1, ovi, 0.0, E, ovi, ncht, part, pe, s, 2)) {
+                if (tk && ladder_gemm_t(2 * Mph, ovi, ovi, 1.0, Yt, ldy, c->P1, c->ldm, 0.0, E, ovi, ncht, part, pe, s, 2)) {
                     // done on the k-major kernel
                 } else if (lad) {
-                    ladder_gemm(2 * Mph, ovi, ovi, 1.0, Y2, ovi, c->P1, ovi, 0.0, E, ovi, nch, part, pe, s, 2);
+                    ladder_gemm(2 * Mph, ovi, ovi, 1.0, Y2, ovi, c->P1, c->ldm, 0.0, E, ovi, nch, part, pe, s, 2);
                 } else {
-                    gemm_rm(2 * Mph, ovi, ovi, 1.0, Y2, ovi, false, c->P1, ovi, false, 0.0, E, ovi, s);
+                    gemm_rm(2 * Mph, ovi, ovi, 1.0, Y2, ovi, false, c->P1, c->ldm, false, 0.0, E, ovi, s);
                 }
                 k_ph_fin(c->sb, D, E, E + (long long)Mph * ovi, nv, o, v, s);
             }
@@ -1875,9 +1908,9 @@ static void m11_adc2(Arena& ws, const double* eo, const double* ev, const Blocks
     double* ovov = take(ws, ov * ov);
     ein(ws, "Qia,Qjb->iajb", 1.0, TV(B.Bov, {X, o, v}), TV(B.Bov, {X, o, v}), 0.0, ovov, s);
     double* T = take(ws, oo * vv);
-    k_amp_t(ovov, eo, ev, o, v, T, s);
+    k_amp_mat(ovov, eo, ev, o, v, ov, nullptr, T, s);
     double* Tt2 = take(ws, oo * vv);
-    k_comb_t(Tt2, T, oo, v, 2.0, -1.0, s);
+    k_pair_comb(Tt2, 0, T, 0, o, v, 2.0, -1.0, s);
     double* P = take(ws, vv);
     ein(ws, "klac,kblc->ab", 1.0, TV(Tt2, {o, o, v, v}), TV(ovov, {o, v, o, v}), 0.0, P, s);
     k_fill(M11, vv, 0.0, s);

@@ -118,27 +118,6 @@ __global__ void split_B_kernel(const double* B, int X, int o, int v, double* Boo
     }
 }
 
-__global__ void amp_t_kernel(const double* ovov, const double* eo, const double* ev, int o, int v, double* T) {
-    long long tot = (long long)o * o * v * v;
-    GRID_STRIDE(t, tot) {
-        int b = (int)(t % v); long long r = t / v;
-        int a = (int)(r % v); r /= v;
-        int j = (int)(r % o); int i = (int)(r / o);
-        double g = ovov[(((long long)i * v + a) * o + j) * v + b];
-        T[t] = g / (eo[i] + eo[j] - ev[a] - ev[b]);
-    }
-}
-
-__global__ void div_d2_kernel(double* Y, const double* eo, const double* ev, int o, int v) {
-    long long tot = (long long)o * o * v * v;
-    GRID_STRIDE(t, tot) {
-        int b = (int)(t % v); long long r = t / v;
-        int a = (int)(r % v); r /= v;
-        int j = (int)(r % o); int i = (int)(r / o);
-        Y[t] /= (eo[i] + eo[j] - ev[a] - ev[b]);
-    }
-}
-
 __global__ void div_d1_kernel(double* y, const double* eo, const double* ev, int o, int v) {
     long long tot = (long long)o * v;
     GRID_STRIDE(t, tot) {
@@ -342,44 +321,53 @@ __global__ void add_diag_kernel(double* A, const double* d, int n) {
 }
 
 // diag[0..v) = diag(M11); diag[v + (i*v + a)*v + b] = K0 + (level>=3) K1 diagonal in z coordinates
-__global__ void diag_adc_kernel(double* diag, const double* M11, const double* eo, const double* ev,
-                                const double* Bvv, const double* oovv, const double* ovov, int o, int v,
-                                int X, int level, double x1) {
+// 32 elements (a, b) per workgroup; the sums over Q on 8 threads each, summed in a fixed order (one thread per
+// element took 92 us at v = 83, X = 249: 27 workgroups, each a chain of X loads)
+__global__ __launch_bounds__(256) void diag_adc_kernel(double* diag, const double* M11, const double* eo, const double* ev,
+                                                       const double* Bvv, const double* h, const double* g, long long ldm,
+                                                       int o, int v, int X, int level, double x1) {
     const double s3 = 1.73205080756887729353;
-    long long vv = (long long)v * v;
-    GRID_STRIDE(t, vv) {
-        int a = (int)(t / v), b = (int)(t % v);
-        if (b == 0) diag[a] = M11[(long long)a * v + a];
-        double aabb = 0.0, abab = 0.0;
+    const long long vv = (long long)v * v;
+    __shared__ double r1[8][33], r2[8][33];
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const long long t = blockIdx.x * 32LL + tx;
+    const bool in = t < vv;
+    const int a = in ? (int)(t / v) : 0, b = in ? (int)(t % v) : 0;
+    double aabb = 0.0, abab = 0.0;
+    if (level >= 3) {
+        for (int Q = ty; Q < X; Q += 8) {
+            const double* BQ = Bvv + (long long)Q * vv;
+            aabb += BQ[(long long)a * v + a] * BQ[(long long)b * v + b];
+            const double x = BQ[(long long)a * v + b];
+            abab += x * x;
+        }
+        r1[ty][tx] = aabb;
+        r2[ty][tx] = abab;
+        __syncthreads();
+        aabb = abab = 0.0;
+        for (int k = 0; k < 8; ++k) { aabb += r1[k][tx]; abab += r2[k][tx]; }
+    }
+    if (!in) return;
+    if (b == 0 && ty == 0) diag[a] = M11[(long long)a * v + a];
+    const double al = 0.5 + 0.5 * s3, be = 0.5 - 0.5 * s3;
+    const double ga = 0.5 + 0.5 / s3, de = 0.5 - 0.5 / s3;
+    for (int i = ty; i < o; i += 8) {
+        double d = ev[a] + ev[b] - eo[i];
         if (level >= 3) {
-            for (int Q = 0; Q < X; ++Q) {
-                const double* BQ = Bvv + (long long)Q * vv;
-                aabb += BQ[(long long)a * v + a] * BQ[(long long)b * v + b];
-                double x = BQ[(long long)a * v + b];
-                abab += x * x;
+            const long long ia = (long long)i * v + a, ib = (long long)i * v + b;
+            const double aaii = h[ia * ldm + ia], bbii = h[ib * ldm + ib];
+            const double aiia = g[ia * ldm + ia], biib = g[ib * ldm + ib];
+            if (a == b) {
+                d += x1 * (aabb - 2.0 * aaii + aiia);
+            } else {
+                const double kabab = aabb - bbii - aaii + 2.0 * biib;
+                const double kbaba = aabb - aaii - bbii + 2.0 * aiia;
+                const double kabba = abab - biib;
+                const double kbaab = abab - aiia;
+                d += x1 * (al * ga * kabab + al * de * kabba + be * ga * kbaab + be * de * kbaba);
             }
         }
-        const double al = 0.5 + 0.5 * s3, be = 0.5 - 0.5 * s3;
-        const double ga = 0.5 + 0.5 / s3, de = 0.5 - 0.5 / s3;
-        for (int i = 0; i < o; ++i) {
-            double d = ev[a] + ev[b] - eo[i];
-            if (level >= 3) {
-                double aaii = oovv[(((long long)i * o + i) * v + a) * v + a];
-                double bbii = oovv[(((long long)i * o + i) * v + b) * v + b];
-                double aiia = ovov[(((long long)i * v + a) * o + i) * v + a];
-                double biib = ovov[(((long long)i * v + b) * o + i) * v + b];
-                if (a == b) {
-                    d += x1 * (aabb - 2.0 * aaii + aiia);
-                } else {
-                    double kabab = aabb - bbii - aaii + 2.0 * biib;
-                    double kbaba = aabb - aaii - bbii + 2.0 * aiia;
-                    double kabba = abab - biib;
-                    double kbaab = abab - aiia;
-                    d += x1 * (al * ga * kabab + al * de * kabba + be * ga * kbaab + be * de * kbaba);
-                }
-            }
-            diag[v + ((long long)i * v + a) * v + b] = d;
-        }
+        diag[v + ((long long)i * v + a) * v + b] = d;
     }
 }
 // ---- fixed-shape block Davidson: convergence and masking decided on the device ----
@@ -615,18 +603,6 @@ void k_split_B(const double* B, int X, int o, int v, double* Boo, double* Bov, d
     hipLaunchKernelGGL(split_B_kernel, dim3(nblocks(n)), dim3(NT), 0, s, B, X, o, v, Boo, Bov, Bvv);
     LAUNCHCHK();
 }
-void k_amp_t(const double* ovov, const double* eo, const double* ev, int o, int v, double* T, hipStream_t s) {
-    if (g_dry) return;
-    long long n = (long long)o * o * v * v;
-    hipLaunchKernelGGL(amp_t_kernel, dim3(nblocks(n)), dim3(NT), 0, s, ovov, eo, ev, o, v, T);
-    LAUNCHCHK();
-}
-void k_div_d2(double* Y, const double* eo, const double* ev, int o, int v, hipStream_t s) {
-    if (g_dry) return;
-    long long n = (long long)o * o * v * v;
-    hipLaunchKernelGGL(div_d2_kernel, dim3(nblocks(n)), dim3(NT), 0, s, Y, eo, ev, o, v);
-    LAUNCHCHK();
-}
 void k_div_d1(double* y, const double* eo, const double* ev, int o, int v, hipStream_t s) {
     if (g_dry) return;
     long long n = (long long)o * v;
@@ -838,12 +814,12 @@ void k_add_diag(double* A, const double* d, int n, hipStream_t s) {
     LAUNCHCHK();
 }
 void k_diag_adc(double* diag, const double* M11, const double* eo, const double* ev, const double* Bvv,
-                const double* oovv, const double* ovov, int o, int v, int X, int level, hipStream_t s, double x1) {
+                const double* h, const double* g, long long ldm, int o, int v, int X, int level, hipStream_t s, double x1) {
     if (g_dry) return;
     long long n = (long long)v * v;
     if (n <= 0) return;
-    hipLaunchKernelGGL(diag_adc_kernel, dim3(nblocks(n)), dim3(NT), 0, s, diag, M11, eo, ev, Bvv, oovv, ovov, o,
-                       v, X, level, x1);
+    hipLaunchKernelGGL(diag_adc_kernel, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, s, diag, M11, eo, ev, Bvv, h, g,
+                       ldm, o, v, X, level, x1);
     LAUNCHCHK();
 }
 

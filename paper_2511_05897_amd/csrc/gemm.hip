@@ -153,6 +153,27 @@ __global__ void splitk_reduce_tree_kernel(const double* part, int nchunk, int M,
     }
 }
 
+// 32 outputs per workgroup, the chunks dealt to 8 threads each (in order), those summed in order: a thread per output
+// walking 45-63 chunks took 15-17 us for 6889 outputs
+__global__ __launch_bounds__(256) void splitk_reduce_wide_kernel(const double* part, int nchunk, int M, int N, double alpha,
+                                                                 double beta, double* C, long long sCm, long long sCn) {
+    const long long MN = (long long)M * N, t = blockIdx.x * 32LL + (threadIdx.x & 31);
+    const int g = threadIdx.x >> 5;
+    double acc = 0.0;
+    if (t < MN)
+        for (int c = g; c < nchunk; c += 8) acc += part[(long long)c * MN + t];
+    __shared__ double red[8][33];
+    red[g][threadIdx.x & 31] = acc;
+    __syncthreads();
+    if (g == 0 && t < MN) {
+        for (int k = 1; k < 8; ++k) acc += red[k][threadIdx.x];
+        const long long m = t / N, n = t % N;
+        double* cp = C + m * sCm + n * sCn;
+        const double v = alpha * acc;
+        *cp = (beta == 0.0) ? v : v + beta * (*cp);
+    }
+}
+
 __global__ void splitk_reduce_kernel(const double* part, int nchunk, int M, int N, double alpha, double beta,
                                      double* C, long long sCm, long long sCn) {
     long long MN = (long long)M * N;
@@ -440,10 +461,13 @@ void launch_tiles(const Gemm& g, hipStream_t s, int tag, long long nb, int sh) {
 void splitk_reduce(const double* part, int nchunk, int M, int N, double alpha, double beta, double* C,
                    long long sCm, long long sCn, hipStream_t s) {
     long long MN = (long long)M * N;
-    if (MN <= 32768 && nchunk >= 64) {
+    if (MN <= 1024 && nchunk >= 64) {
         // few outputs, many chunks: one block per output, chunks spread over its threads
         hipLaunchKernelGGL(splitk_reduce_tree_kernel, dim3((unsigned)MN), dim3(256), 0, s, part, nchunk, M, N, alpha,
                            beta, C, sCm, sCn);
+    } else if (nchunk >= 12 && MN <= 65536) {
+        hipLaunchKernelGGL(splitk_reduce_wide_kernel, dim3((unsigned)((MN + 31) / 32)), dim3(256), 0, s, part, nchunk, M, N,
+                           alpha, beta, C, sCm, sCn);
     } else {
         unsigned gb = (unsigned)std::min<long long>((MN + 255) / 256, 4096);
         hipLaunchKernelGGL(splitk_reduce_kernel, dim3(gb), dim3(256), 0, s, part, nchunk, M, N, alpha, beta, C, sCm,
@@ -523,13 +547,17 @@ GemmScratch::~GemmScratch() {
     g_gemm_scratch_n = prev_n;
 }
 
-static void gemm_impl(const Gemm& g, hipStream_t s, int tag, int kmin_split);
+// a single GEMM with few output tiles splits K from here on, into chunks of at least 64: four tiles of 64 x 64 over
+// K = 2241 took 171 us in one chunk (140 slabs, each a load's latency), 13 + 5 us in 18
+constexpr int KMIN_SPLIT = 192;
 
-void gemm(const Gemm& g, hipStream_t s, int tag) { gemm_impl(g, s, tag, 4096); }
-
-void gemm_split(const Gemm& g, hipStream_t s, int tag) { gemm_impl(g, s, tag, 512); }
-
-static void gemm_impl(const Gemm& g, hipStream_t s, int tag, int kmin_split) {
+void gemm(const Gemm& gin, hipStream_t s, int tag) {
+    constexpr int kmin_split = KMIN_SPLIT;
+    Gemm g = gin;
+    if (g.nb0 == 1 && g.Klast >= 0) {  // a single K chunk: its length is the ragged one
+        g.K = g.Klast;
+        g.Klast = -1;
+    }
     if (g_dry) return;
     if (g.M <= 0 || g.N <= 0) return;
     long long nb = (long long)g.nb0 * g.nb1;
@@ -587,7 +615,7 @@ static void gemm_impl(const Gemm& g, hipStream_t s, int tag, int kmin_split) {
     if (nb == 1 && tiles < 256 && g.K >= kmin_split && g_gemm_scratch) {
         // about 512 workgroups (2 per CU): at o=20 v=200 the 1p coupling product (one tile, K = o v^2)
         // takes 291 + 8 us (GEMM + reduction) with 512 chunks, 306 + 21 us with 2048, 385 + 6 us with 256
-        long long nchunk = std::min<long long>((g.K + 255) / 256, (512 + tiles - 1) / tiles);
+        long long nchunk = std::min<long long>((g.K + 63) / 64, (512 + tiles - 1) / tiles);
         nchunk = std::min<long long>(nchunk, g_gemm_scratch_n / std::max<long long>(MN, 1));
         nchunk = std::min<long long>(nchunk, 65535);
         if (nchunk >= 2) {

@@ -70,8 +70,6 @@ struct Gemm {
     int Klast = -1;  // if >= 0: K of the batches with b0 == nb0-1 (ragged last K chunk)
 };
 void gemm(const Gemm& g, hipStream_t s, int tag = 0);
-// as gemm, but a single GEMM with few output tiles splits K from K >= 512 on (gemm: K >= 4096)
-void gemm_split(const Gemm& g, hipStream_t s, int tag = 0);
 // reduced-precision GEMM, FP32 accumulation, FP64 C (see gemm_lp.hip):
 // A FP64 (converted on load), B in the reduced type (prec 1: float, 2: bf16)
 struct GemmLP {
@@ -118,6 +116,11 @@ bool ladder_t_supported(int M, int N, int K, const double* Zt, long long ldz, co
 bool ladder_gemm_t(int M, int N, int K, double alpha, const double* Zt, long long ldz, const double* G, long long ldg,
                    double beta, double* C, long long ldc, int nchunk, double* partial, long long partial_elems,
                    hipStream_t s, int tag = 0);  // tag: 0 sigma ladder, 1 tuner trial, 2 other GEMM
+// the same with the row tiling (mtiles tiles of 16 tm rows) and K per chunk (a multiple of 16, within the 32-bit
+// offsets) given by the caller
+void ladder_gemm_t_shape(int M, int N, int K, double alpha, const double* Zt, long long ldz, const double* G,
+                         long long ldg, double beta, double* C, long long ldc, int tm, int mtiles, int kc, double* partial,
+                         hipStream_t s);
 // FP32 operands (FP32 accumulation, FP64 partial sums / output), Z k-major, ldz and ldg multiples of 4
 int ladder_t32_min_chunks(int K, long long ldz, long long ldg);
 bool ladder_t32_supported(int M, int N, int K, const float* Zt, long long ldz, const float* G, long long ldg);
@@ -188,10 +191,21 @@ void k_axpby(double* y, const double* x, long long n, double a, double b, hipStr
 void k_permute4(double* out, const double* in, const int din[4], const int perm[4], double alpha,
                 double beta, hipStream_t s);
 void k_split_B(const double* B, int X, int o, int v, double* Boo, double* Bov, double* Bvv, hipStream_t s);
-// T[i][j][a][b] = ovov[i][a][j][b] / (eo_i + eo_j - ev_a - ev_b)
-void k_amp_t(const double* ovov, const double* eo, const double* ev, int o, int v, double* T, hipStream_t s);
-// Y[i][j][a][b] /= (eo_i + eo_j - ev_a - ev_b)
-void k_div_d2(double* Y, const double* eo, const double* ev, int o, int v, hipStream_t s);
+// setup matrices over occupied-virtual pairs (setup_mats.hip): g [(ia)][(jb)] with rows of ld
+// T[i][j][a][b] = g / (eo_i + eo_j - ev_a - ev_b), and as the matrix Tm[(ia)][(jb)] (nullable)
+void k_amp_mat(const double* g, const double* eo, const double* ev, int o, int v, long long ld, double* Tm, double* T,
+               hipStream_t s);
+// out(i,j,a,b) = ca in(i,j,a,b) + cb in(i,j,b,a); ld 0: blocks [i][j][a][b], else a matrix [(ia)][(jb)] with rows of ld
+void k_pair_comb(double* out, long long ldo, const double* in, long long ldi, int o, int v, double ca, double cb,
+                 hipStream_t s);
+// second-order doubles U[(ia)][(jb)] from LH [i][j][a][b] (ladder and hole-hole terms) and the products RB, RC
+void k_doubles(double* U, const double* LH, const double* RB, const double* RC, const double* eo, const double* ev, int o,
+               int v, long long ld, hipStream_t s);
+// G2[(k,d)][(a,c)] = V1[(k,a)][(c,d)], a < nc
+void k_ovvv_perm(double* G2, long long ldg, const double* V1, int o, int nc, int v, hipStream_t s);
+// U_z rows of a chunk from its parts (C1, C2 null: first order only)
+void k_uz_form(double* Uz, const double* F, const double* C1, const double* C2, long long ldc, double x2, int nc, int o,
+               int v, hipStream_t s);
 void k_div_d1(double* y, const double* eo, const double* ev, int o, int v, hipStream_t s);
 // out = a*T + b*T^(ab swapped), T[n][v][v] blocks
 void k_comb_t(double* out, const double* T, long long nblk, int v, double a, double b, hipStream_t s);
@@ -275,9 +289,9 @@ void k_symmetrize(double* A, int n, hipStream_t s);   // A = (A + A^T)/2
 // G[(m0+j)*ld + i] = G[i*ld + m0 + j] for i < m0 + nc, j < nc  (new columns mirrored into rows)
 void k_mirror_cols(double* G, int ld, int m0, int nc, hipStream_t s);
 void k_add_diag(double* A, const double* d, int n, hipStream_t s);
-// diagonal of M; x1 scales the first-order 2p1h terms (level 3; sm-ADC)
+// diagonal of M (h, g: the pair matrices (ij|ab), (ia|jb)); x1 scales the first-order 2p1h terms (level 3; sm-ADC)
 void k_diag_adc(double* diag, const double* M11, const double* eo, const double* ev, const double* Bvv,
-                const double* oovv, const double* ovov, int o, int v, int X, int level, hipStream_t s,
+                const double* h, const double* g, long long ldm, int o, int v, int X, int level, hipStream_t s,
                 double x1 = 1.0);
 
 // ---------------------------------------------------------------------------

@@ -844,6 +844,21 @@ bool ladder_gemm_t(int M, int N, int K, double alpha, const double* Zt, long lon
     return true;
 }
 
+void ladder_gemm_t_shape(int M, int N, int K, double alpha, const double* Zt, long long ldz, const double* G,
+                         long long ldg, double beta, double* C, long long ldc, int tm, int mtiles, int kc, double* partial,
+                         hipStream_t s) {
+    LadderArgs a;
+    a.Z = Zt; a.ldz = ldz; a.G = G; a.ldg = ldg; a.C = C; a.ldc = ldc; a.P = partial;
+    a.M = M; a.N = N; a.K = K;
+    a.Kc = kc;
+    a.nchunk = (K + kc - 1) / kc;
+    a.ntn = (N + LBN - 1) / LBN;
+    a.alpha = alpha; a.beta = beta;
+    launch_t_tag<2>(a, tm, mtiles, s);
+    LAUNCHCHK();
+    if (a.nchunk > 1) splitk_reduce(partial, a.nchunk, M, N, alpha, beta, C, ldc, 1, s);
+}
+
 int ladder_t32_min_chunks(int K, long long ldz, long long ldg) {
     const long long ld = std::max(ldz, ldg);
     if (K <= 0 || ld <= 0) return 0;

@@ -5,6 +5,10 @@
 
 namespace adc3 {
 
+// C(m,n) = alpha sum_k A[k][m] B[k][n] + beta C(m,n), C rows of ldc; temporaries (even-stride copies) from ws
+void gemm_km(Arena& ws, long long M, long long N, long long K, double alpha, const double* A, long long lda,
+             const double* B, long long ldb, double beta, double* C, long long ldc, hipStream_t s);
+
 void ein2(Arena& ws, const char* spec, double alpha, const double* A, const int* adims, const double* B,
           const int* bdims, double beta, double* C, hipStream_t s);
 

@@ -12,6 +12,7 @@
 #include "internal.h"
 #include "tensor.h"
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 
 namespace adc3 {
@@ -56,6 +57,65 @@ void permute_any(double* out, const double* in, const std::string& from, const i
 }
 }  // namespace
 
+// The tile and K split of a k-major product: the least modelled time over row tiles of 16 tm rows and K chunks.
+// A workgroup's slab of 16 k keeps each of a CU's four matrix cores busy for 512 tm cycles; a CU with one workgroup
+// also waits for the slab's loads (about 700 cycles), with two that overlaps; a split adds a pass over the partial
+// sums and a launch.
+static void km_shape(long long M, long long N, long long K, long long partial, int kcmax, int& tm, int& mt, int& kc) {
+    const long long ntn = (N + 127) / 128, nb = (M + 15) / 16;
+    double best = 1e300;
+    for (int t = (int)std::min<long long>(8, nb); t >= 1; --t) {
+        const long long m = (nb + t - 1) / t;
+        if (m > 65535) continue;
+        for (int c = 1; c <= 32; ++c) {
+            const long long k = ((K + c - 1) / c + 15) / 16 * 16, n = (K + k - 1) / k;
+            if (k > kcmax || (n > 1 && n * M * N > partial) || (c > 1 && k < 64)) continue;
+            const double w = (double)m * ntn * n, slabs = (double)k / 16;
+            double cost = std::ceil(w / 256.0) * slabs * (512.0 * t + (w <= 256 ? 700.0 : 400.0)) + 3000.0;
+            if (n > 1) cost += 7000.0 + 2.2e9 * (8.0 * (n + 1) * M * N) / 3.5e12;
+            if (cost < best) { best = cost; tm = t; mt = (int)m; kc = (int)k; }
+        }
+    }
+}
+
+void gemm_km(Arena& ws, long long M, long long N, long long K, double alpha, const double* A, long long lda,
+             const double* B, long long ldb, double beta, double* C, long long ldc, hipStream_t s) {
+    if (M <= 0 || N <= 0) return;
+    const size_t mark = ws.mark();
+    // 16-byte rows (offsets relative to the workspace, so that the counting dry runs decide alike)
+    const uintptr_t base = ws.base ? (uintptr_t)ws.base : ARENA_COUNT_BASE;
+    auto even = [&](const double* X, long long& ld, long long cols) {
+        if (ld % 2 == 0 && (((uintptr_t)X - base) & 15) == 0) return X;
+        const long long n = cols + (cols & 1);
+        double* t = ws.take<double>((size_t)std::max<long long>(K * n, 1));
+        k_copy2d(t, n, X, ld, K, cols, 1.0, 0.0, s);
+        ld = n;
+        return (const double*)t;
+    };
+    const bool tile = 2.0 * (double)M * (double)N * (double)K >= 4e6 && M >= 16 && N >= 32 && K >= 16;
+    if (tile) {
+        A = even(A, lda, M);
+        B = even(B, ldb, N);
+        if (!g_dry && ladder_t_supported((int)M, (int)N, (int)K, A, lda, B, ldb) && ladder_t_min_chunks((int)K, lda, ldb) == 1) {
+            int tm = 0, mt = 0, kc = 0;
+            km_shape(M, N, K, g_gemm_scratch ? g_gemm_scratch_n : 0, (int)((K + 15) / 16 * 16), tm, mt, kc);
+            if (tm > 0) {
+                ladder_gemm_t_shape((int)M, (int)N, (int)K, alpha, A, lda, B, ldb, beta, C, ldc, tm, mt, kc, g_gemm_scratch, s);
+                ws.release(mark);
+                return;
+            }
+        }
+    }
+    Gemm g;
+    g.M = (int)M; g.N = (int)N; g.K = (int)K;
+    g.A = A; g.sAm = 1; g.sAk = lda;
+    g.B = B; g.sBk = ldb; g.sBn = 1;
+    g.C = C; g.sCm = ldc; g.sCn = 1;
+    g.alpha = alpha; g.beta = beta;
+    gemm(g, s);
+    ws.release(mark);
+}
+
 void ein2(Arena& ws, const char* spec, double alpha, const double* A, const int* adims, const double* B,
           const int* bdims, double beta, double* C, hipStream_t s) {
     Parsed p = parse(spec);
@@ -88,50 +148,51 @@ void ein2(Arena& ws, const char* spec, double alpha, const double* A, const int*
     g.M = (int)M; g.N = (int)N; g.K = (int)K;
     g.alpha = alpha;
     if (M > 2147483647LL || N > 2147483647LL || K > 2147483647LL) fail(-1, "ein2: dimension too large");
-    // A large contraction gets row-major B and output and a contiguous A (a permute of each is cheap
-    // next to the GEMM), so that it runs on the ladder tiles: A k-major ([K..,M..], both tiles copied
-    // straight into LDS; K in consecutive ranges when one launch's 32-bit offsets cannot span it), else
-    // row-major
-    const bool big = 2.0 * (double)M * (double)N * (double)K >= 4e9;
-    const long long ldn = N + (N & 1);  // B's row stride on the k-major path: even, for 16-byte rows
-    const bool kmajor = big && M >= 128 && N >= 128 && ((M + 127) / 128) * ((N + 127) / 128) >= 512 &&
-                        ladder_t_min_chunks((int)K, M + (M & 1), ldn) >= 1;
-    // A
+    // A contraction of some size runs on the k-major tiles (gemm_km): both operands as [K..][M..], [K..][N..], in
+    // place or permuted once (cheap next to the GEMM), row-major output; where the output reads [N..][M..] the
+    // operands change places.  Measured at o=9 v=83: the 64 x 64 tile with operands through registers takes 51 us
+    // for 747^3 (144 workgroups, a load's latency per 16-deep slab), this path 17-25 us.
+    const bool kmajor = 2.0 * (double)M * (double)N * (double)K >= 5e7 && M >= 32 && N >= 32 && K >= 16;
     if (kmajor) {
-        if (p.a == Kl + Ml && M % 2 == 0) { g.A = A; g.sAm = 1; g.sAk = M; }
-        else {
-            const long long ldm = M + (M & 1);  // even, for 16-byte rows
-            double* t = ws.take<double>(K * ldm);
-            if (ldm == M) {
-                permute_any(t, A, p.a, adims, Kl + Ml, 1.0, 0.0, s);
-            } else {
-                double* u = ws.take<double>(K * M);
-                permute_any(u, A, p.a, adims, Kl + Ml, 1.0, 0.0, s);
-                k_copy2d(t, ldm, u, M, K, M, 1.0, 0.0, s);
-            }
-            g.A = t; g.sAm = 1; g.sAk = ldm;
+        const bool swap = p.o == Nl + Ml;
+        const double *X = swap ? B : A, *Y = swap ? A : B;
+        const std::string &xl = swap ? p.b : p.a, &yl = swap ? p.a : p.b, &rl = swap ? Nl : Ml, &cl = swap ? Ml : Nl;
+        const int *xd = swap ? bdims : adims, *yd = swap ? adims : bdims;
+        const long long R = swap ? N : M, Cc = swap ? M : N;
+        if (xl != Kl + rl) {
+            double* t = ws.take<double>(K * R);
+            permute_any(t, X, xl, xd, Kl + rl, 1.0, 0.0, s);
+            X = t;
         }
-    } else if (p.a == Ml + Kl) { g.A = A; g.sAm = K; g.sAk = 1; }
-    else if (p.a == Kl + Ml && !big) { g.A = A; g.sAm = 1; g.sAk = M; }
+        if (yl != Kl + cl) {
+            double* t = ws.take<double>(K * Cc);
+            permute_any(t, Y, yl, yd, Kl + cl, 1.0, 0.0, s);
+            Y = t;
+        }
+        if (p.o == rl + cl) {
+            gemm_km(ws, R, Cc, K, alpha, X, R, Y, Cc, beta, C, Cc, s);
+        } else {
+            double* t = ws.take<double>(M * N);
+            gemm_km(ws, R, Cc, K, alpha, X, R, Y, Cc, 0.0, t, Cc, s);
+            int tdims[4];
+            const std::string tl = rl + cl;
+            for (size_t k = 0; k < tl.size(); ++k) tdims[k] = odims[p.o.find(tl[k])];
+            permute_any(C, t, tl, tdims, p.o, 1.0, beta, s);
+        }
+        ws.release(mark);
+        return;
+    }
+    // A
+    if (p.a == Ml + Kl) { g.A = A; g.sAm = K; g.sAk = 1; }
+    else if (p.a == Kl + Ml) { g.A = A; g.sAm = 1; g.sAk = M; }
     else {
         double* t = ws.take<double>(M * K);
         permute_any(t, A, p.a, adims, Ml + Kl, 1.0, 0.0, s);
         g.A = t; g.sAm = K; g.sAk = 1;
     }
     // B
-    if (kmajor && !(p.b == Kl + Nl && ldn == N && ((uintptr_t)B & 15) == 0)) {
-        // [K][N] with an even row stride
-        double* t = ws.take<double>(K * ldn);
-        if (ldn == N) {
-            permute_any(t, B, p.b, bdims, Kl + Nl, 1.0, 0.0, s);
-        } else {
-            double* u = ws.take<double>(K * N);
-            permute_any(u, B, p.b, bdims, Kl + Nl, 1.0, 0.0, s);
-            k_copy2d(t, ldn, u, N, K, N, 1.0, 0.0, s);
-        }
-        g.B = t; g.sBk = ldn; g.sBn = 1;
-    } else if (p.b == Kl + Nl) { g.B = B; g.sBk = N; g.sBn = 1; }
-    else if (p.b == Nl + Kl && !big) { g.B = B; g.sBk = 1; g.sBn = K; }
+    if (p.b == Kl + Nl) { g.B = B; g.sBk = N; g.sBn = 1; }
+    else if (p.b == Nl + Kl) { g.B = B; g.sBk = 1; g.sBn = K; }
     else {
         double* t = ws.take<double>(K * N);
         permute_any(t, B, p.b, bdims, Kl + Nl, 1.0, 0.0, s);
@@ -139,7 +200,7 @@ void ein2(Arena& ws, const char* spec, double alpha, const double* A, const int*
     }
     // C
     if (p.o == Ml + Nl) { g.C = C; g.sCm = N; g.sCn = 1; g.beta = beta; gemm(g, s); }
-    else if (p.o == Nl + Ml && !big) { g.C = C; g.sCm = 1; g.sCn = M; g.beta = beta; gemm(g, s); }
+    else if (p.o == Nl + Ml) { g.C = C; g.sCm = 1; g.sCn = M; g.beta = beta; gemm(g, s); }
     else {
         double* t = ws.take<double>(M * N);
         g.C = t; g.sCm = N; g.sCn = 1; g.beta = 0.0;
