@@ -125,8 +125,10 @@ struct Ctx {
     // block G- [sa_lm(v)]^2 (Gm points at it)
     double *G = nullptr, *Gm = nullptr;
     bool df = false;          // ladder assembled from Bvv in every application instead of stored
-    double* P1 = nullptr;     // (ij|bd) as [(i,b)][(j,d)] with rows of ldm, level 3
-    double *zb = nullptr, *xb = nullptr, *xtb = nullptr, *sdb = nullptr, *sb = nullptr;
+    // level 3: PB [X + ov][ldm] holds -Bov and, from row X on, P1 = (ij|bd) as [(i,b)][(j,d)]; BovT [(j,d)][Q], rows of ldx
+    double *P1 = nullptr, *PB = nullptr, *BovT = nullptr;
+    long long ldx = 0;
+    double *zb = nullptr, *sb = nullptr;
     long long sigma_count = 0;
     // reduced-precision copies (precision 1: FP32 ladder and coupling; 2: BF16 ladder, FP32 coupling)
     int prec = 0;
@@ -208,7 +210,14 @@ static Ctx* build_ctx(Arena& ws, const double* eo_in, const double* ev_in, const
     c->u1 = take(ws, ov);
     c->diag = take(ws, c->N);
     c->Uz = take(ws, v * (long long)o * vv);
-    if (level >= 3) c->P1 = take(ws, ov * ldm);
+    if (level >= 3) {
+        c->PB = take(ws, (X + ov) * ldm);
+        c->P1 = c->PB + X * ldm;
+        c->ldx = X + (X & 1);
+        c->BovT = take(ws, ov * c->ldx);
+        k_copy2d(c->PB, ldm, Bov, ov, X, ov, -1.0, 0.0, s);
+        k_transpose(Bov, ov, X, ov, c->BovT, c->ldx, s);
+    }
     if (prec > 0) {
         c->Uz32 = ws.take<float>((size_t)std::max<long long>(v * (long long)o * vv, 1));
         if (level >= 3) {
@@ -223,13 +232,10 @@ static Ctx* build_ctx(Arena& ws, const double* eo_in, const double* ev_in, const
         }
     }
     c->mlp_wb = ws.take<unsigned short>(256 * 256);
-    c->zb = take(ws, NVMAX * (long long)o * vv);
-    // xb, xtb, sdb are contiguous: before the particle-hole terms use them they hold the
-    // ladder's split-K partial sums
-    c->xb = take(ws, 3 * NVMAX * (long long)o * vv);
-    c->xtb = c->xb + NVMAX * (long long)o * vv;
-    c->sdb = c->xtb + NVMAX * (long long)o * vv;
-    c->sb = take(ws, NVMAX * (long long)o * vv);
+    // one buffer of five blocks of vectors: the stored ladder's partial sums, or (assembled ladder) its input zb and
+    // result sb
+    c->zb = take(ws, 5 * NVMAX * (long long)o * vv);
+    c->sb = c->zb + NVMAX * (long long)o * vv;
     c->gin = take(ws, NVMAX * c->N);
     c->gout = take(ws, NVMAX * c->N);
     c->sig_bytes = sigma_region_bytes(c);
@@ -540,6 +546,10 @@ static Ctx* build_ctx(Arena& ws, const double* eo_in, const double* ev_in, const
     return c;
 }
 
+// Pair blocks from this size on stream G from HBM in every application; below, both fit the last-level cache (2 x 134 MB)
+// and a short product is bound by latency and launches (o=4 v=20: 22 us as two launches and their reductions, 5 as one).
+constexpr long long LADDER_STREAM_MIN = 4096;
+
 // sigma = M r for nvec vectors
 // One pass of at most NVMAX vectors: ss[nv][N] = M rr[nv][N], temporaries from ws.
 static void sigma_pass(Ctx* c, Arena& ws, const double* rr, double* ss, int nv, hipStream_t s, int prec) {
@@ -547,41 +557,28 @@ static void sigma_pass(Ctx* c, Arena& ws, const double* rr, double* ss, int nv, 
     const int o = c->o, v = c->v;
     const long long N = c->N, vv = (long long)v * v, ovv = (long long)o * vv;
     {
-        // 1p: M11 r1 + U_z z
-        gemm_rm(nv, v, v, 1.0, rr, N, false, c->M11, v, true, 0.0, ss, N, s);
-        if (prec > 0) {
-            // the FP32 copy of U_z: both products in one stream over it when it fits the fused kernel (sums in
-            // FP64), else the two reduced-precision GEMMs (FP32 sums)
-            const long long pe1 = v <= 256 ? 768LL * nv * v : 0;
-            double* part1 = pe1 > 0 ? take(ws, pe1) : nullptr;
-            const long long nch = (g_dry || pe1 == 0)
-                                      ? 0
-                                      : couple_fused32(nv, v, ovv, c->Uz32, ovv, rr + v, N, rr, N, ss + v, N, part1, pe1, s);
-            if (nch > 0) {
-                splitk_reduce(part1, (int)nch, nv, v, 1.0, 1.0, ss, N, 1, s);
-            } else {
+        // 1p rows and coupling: both U_z products (1p: U_z z, 2p1h: U_z^T r1) in one stream over U_z with M11 r1 and the
+        // zeroth-order 2p1h diagonal, when it fits the fused kernel (v <= 256); FP32: the FP32 copy of U_z, FP64 sums
+        const long long pe1 = v <= 256 ? 768LL * nv * v : 0;
+        double* part1 = pe1 > 0 ? take(ws, pe1) : nullptr;
+        const bool fused = !g_dry && pe1 > 0 &&
+                           couple_fused(nv, v, ovv, c->Uz, prec > 0 ? c->Uz32 : nullptr, ovv, rr, ss, N, c->M11, c->eo, c->ev,
+                                        part1, pe1, s);
+        if (!fused) {
+            gemm_rm(nv, v, v, 1.0, rr, N, false, c->M11, v, true, 0.0, ss, N, s);
+            if (prec > 0) {
                 GemmLP g;
                 g.M = nv; g.N = v; g.K = (int)ovv;
                 g.A = rr + v; g.sAm = N; g.sAk = 1;
                 g.B = c->Uz32; g.sBk = 1; g.sBn = ovv;
                 g.C = ss; g.sCm = N; g.sCn = 1; g.beta = 1.0;
-                gemm_lp(g, 1, s);
+                if (!g_dry) gemm_lp(g, 1, s);
                 GemmLP h;
                 h.M = nv; h.N = (int)ovv; h.K = v;
                 h.A = rr; h.sAm = N; h.sAk = 1;
                 h.B = c->Uz32; h.sBk = ovv; h.sBn = 1;
                 h.C = ss + v; h.sCm = N; h.sCn = 1;
-                gemm_lp(h, 1, s);
-            }
-        } else {
-            // both U_z products (1p: U_z z, 2p1h: U_z^T r1) in one stream over U_z when it fits the fused
-            // kernel (v <= 256, aligned rows), else one stream each
-            const long long pe1 = v <= 256 ? 768LL * nv * v : 0;
-            double* part1 = pe1 > 0 ? take(ws, pe1) : nullptr;
-            const long long nch =
-                (g_dry || pe1 == 0) ? 0 : couple_fused(nv, v, ovv, c->Uz, ovv, rr + v, N, rr, N, ss + v, N, part1, pe1, s);
-            if (nch > 0) {
-                splitk_reduce(part1, (int)nch, nv, v, 1.0, 1.0, ss, N, 1, s);
+                if (!g_dry) gemm_lp(h, 1, s);
             } else {
                 gemm_rm(nv, v, (int)ovv, 1.0, rr + v, N, false, c->Uz, ovv, true, 1.0, ss, N, s);
                 // 2p1h: U_z^T r1, a stream over U_z [a][(i,b,c)]: on the k-major ladder kernel with r1
@@ -594,162 +591,161 @@ static void sigma_pass(Ctx* c, Arena& ws, const double* rr, double* ss, int nv, 
                 if (!(t && ladder_gemm_t(nv, (int)ovv, v, 1.0, r1t, ldr, c->Uz, ovv, 0.0, ss + v, N, 1, nullptr, 0, s, 2)))
                     gemm_rm(nv, (int)ovv, v, 1.0, rr, N, false, c->Uz, ovv, false, 0.0, ss + v, N, s);
             }
+            k_k0_add(ss + v, rr + v, c->eo, c->ev, o, v, nv, N, s);
         }
-        k_k0_add(ss + v, rr + v, c->eo, c->ev, o, v, nv, N, s);
-        if (c->level >= 3) {
-            double* zb = c->zb;
-            k_copy2d(zb, ovv, rr + v, N, nv, ovv, 1.0, 0.0, s);
-            // ladder: sum_cd (ac|bd) z_cd  (G symmetric)
-            if (c->df) {
-                // assembled from Bvv: 4 X M v^3 flops; the intermediate is written and read once (and its
-                // region is reused by the particle-hole terms below)
-                const size_t mk = ws.mark();
-                const int M = nv * o, X = c->X;
-                const long long ve = df_v_elems(M, v, X);
-                const double eb = prec == 0 ? 8.0 : prec == 1 ? 4.0 : 2.0;
-                const double fl = 4.0 * X * (double)M * v * (double)vv;
-                const double by = eb * (2.0 * X * (double)M * vv + (double)X * vv + M * (double)vv) + 8.0 * M * (double)vv;
-                const double pk = prec == 0 ? PEAK_FP64_MFMA : prec == 1 ? PEAK_FP32_MFMA : PEAK_BF16_MFMA;
-                ProfScope p(prec > 0 ? PROF_LADDER_LP : PROF_LADDER, s, fl, by, 1e3 * std::max(fl / pk, by / PEAK_HBM));
-                if (prec > 0) {
-                    const long long vl = prec == 2 ? ve + (long long)M * vv + 8 : ve;  // BF16: + Z transposed
-                    void* V = prec == 1 ? (void*)ws.take<float>((size_t)vl) : (void*)ws.take<unsigned short>((size_t)vl);
-                    k_to_lowp(c->zlo, zb, (long long)M * vv, prec, s);
-                    // FP32 sigma of a BF16 context (its middle phase) takes the FP32 copy of Bvv
-                    const void* Bl = (prec == 1 && c->prec == 2) ? (const void*)c->Bvv32 : c->Bvvlo;
-                    df_ladder(prec, M, v, X, Bl, c->zlo, c->sb, false, V, vl, s);
-                } else {
-                    double* V = take(ws, ve);
-                    df_ladder(0, M, v, X, c->Bvv, zb, c->sb, false, V, ve, s);
-                }
-                ws.release(mk);
+        if (c->level < 3) return;
+        // operands of the ladder and of the particle-hole products, one pass over z.  The particle-hole terms on the
+        // alpha-beta determinants x (z = S + sqrt3 A of x per block):
+        //   d[n][i][a][b] = sum_jd (ib|jd) xt[n][j][a][d] - (ij|bd) x[n][j][a][d] - (ij|ad) x[n][j][d][b]
+        // as one k-major product of stacked rows, -d = E2[(n,a)][(i,b)] + E3[(n,b)][(i,a)]:
+        //   E = [Wq 0; Y2t Y3t]^T [-Bov; (ij|bd)]  over k = (Q; (j,d)), rows ((n,a) of E2, (n,a) of E3),
+        // where Wq[Q][(n,a)] = sum_jd Bov[Q][(j,d)] Y1t[(j,d)][(n,a)] carries the (ib|jd) product through the DF factor
+        // (its contraction indices sit in one factor); the E3 rows start past the Q part.
+        const int M = nv * o, X = c->X, Mph = nv * v, ovi = o * v;
+        const long long lp = sa_lp(v), lm = sa_lm(v);
+        const long long ldy = 2LL * Mph, ldy1 = Mph + (Mph & 1);
+        double* Yt = take(ws, ((long long)X + ovi) * 2 * NVMAX * v);
+        double* Y1t = take(ws, (long long)ovi * (NVMAX * v + 1));
+        double* Y23 = Yt + X * ldy;
+        // The ladder's partial sums take the context's five sigma buffers.
+        double* pbuf = c->zb;
+        const long long pe = 5LL * NVMAX * o * vv;
+        // FP64 and FP32 with >= 3 row blocks (33 rows and up): the packed rows k-major, for the kernel that copies both
+        // tiles straight into LDS (below that the G stream bounds the product and the row-major kernel, with more
+        // workgroups per CU, streams it faster: 588 against 610 us per block at 20 rows, v = 200); both blocks in one
+        // launch where the partial sums of both fit.  Fewer rows of a block below the streaming sizes: whichever of the
+        // two measures faster.
+        int ltm, lmt, tm = 0, mt = 0, kc = 0;
+        ladder_rows(M, ltm, lmt);
+        const bool stored = !c->df, rows3 = prec <= 1 && ltm >= 3;
+        const long long ldt8 = (M + 1) / 2 * 2, ldt4 = (M + 3) / 4 * 4;
+        const bool km64 = stored && prec == 0 && (rows3 || lp < LADDER_STREAM_MIN);
+        double* W = stored ? take(ws, ((long long)M + 3) * (lp + lm)) : nullptr;
+        double* CW = stored ? take(ws, (long long)M * (lp + lm)) : nullptr;
+        bool dual = km64 && ladder_t_shape(M, lp, lm, ldt8, pe, tm, mt, kc);
+        LadderTProb pr[2];
+        if (dual) {
+            const long long nch = (lp + kc - 1) / kc;
+            pr[0] = LadderTProb{(int)lp, (int)lp, W, ldt8, c->G, lp, pbuf};
+            pr[1] = LadderTProb{(int)lm, (int)lm, W + ldt8 * lp, ldt8, c->Gm, lm, pbuf + nch * M * lp};
+            if (!g_dry && !rows3 && !ladder_dual_tuned(pr, lm > 0 ? 2 : 1, M, tm, mt, kc, CW, pbuf, pe, s))
+                dual = false;
+        }
+        const long long nmin = km64 ? ladder_t_min_chunks((int)lp, ldt8, lp) : 0;
+        const bool kmajor = prec == 0 ? dual || (rows3 && nmin > 0 && nmin * M * lp <= pe) : stored && rows3;
+        const long long ldt = !kmajor ? 0 : prec == 1 ? ldt4 : ldt8;
+        const long long woff = kmajor ? ldt * lp : (long long)M * lp;
+        double* Wm = stored ? W + woff : nullptr;
+        k_sigma_prep(rr + v, N, nv, o, v, W, Wm, ldt, Y1t, ldy1, Yt, X, Y23, ldy, s);
+        // ladder: sum_cd (ac|bd) z_cd  (G symmetric)
+        int nl = 1;
+        const double *Cs = nullptr, *Cm = nullptr;
+        if (c->df) {
+            // assembled from Bvv: 4 X M v^3 flops; the intermediate is written and read once
+            const size_t mk = ws.mark();
+            k_copy2d(c->zb, ovv, rr + v, N, nv, ovv, 1.0, 0.0, s);
+            const long long ve = df_v_elems(M, v, X);
+            const double eb = prec == 0 ? 8.0 : prec == 1 ? 4.0 : 2.0;
+            const double fl = 4.0 * X * (double)M * v * (double)vv;
+            const double by = eb * (2.0 * X * (double)M * vv + (double)X * vv + M * (double)vv) + 8.0 * M * (double)vv;
+            const double pk = prec == 0 ? PEAK_FP64_MFMA : prec == 1 ? PEAK_FP32_MFMA : PEAK_BF16_MFMA;
+            ProfScope p(prec > 0 ? PROF_LADDER_LP : PROF_LADDER, s, fl, by, 1e3 * std::max(fl / pk, by / PEAK_HBM));
+            if (prec > 0) {
+                const long long vl = prec == 2 ? ve + (long long)M * vv + 8 : ve;  // BF16: + Z transposed
+                void* V = prec == 1 ? (void*)ws.take<float>((size_t)vl) : (void*)ws.take<unsigned short>((size_t)vl);
+                k_to_lowp(c->zlo, c->zb, (long long)M * vv, prec, s);
+                // FP32 sigma of a BF16 context (its middle phase) takes the FP32 copy of Bvv
+                const void* Bl = (prec == 1 && c->prec == 2) ? (const void*)c->Bvv32 : c->Bvvlo;
+                df_ladder(prec, M, v, X, Bl, c->zlo, c->sb, false, V, vl, s);
             } else {
-                // stored ladder through its pair blocks: w+- = pack(z), C+- = w+- G+-, sigma_z = unpack(C+-);
-                // one profiled launch per block
-                const int M = nv * o;
-                const long long lp = sa_lp(v), lm = sa_lm(v);
-                const size_t mk = ws.mark();
-                double* W = take(ws, (long long)M * (lp + lm));
-                double* CW = take(ws, (long long)M * (lp + lm));
-                const long long pe = 3 * NVMAX * (long long)o * vv;
-                k_sa_pack(zb, vv, M, v, W, W + (long long)M * lp, s);
-                if (prec > 0) k_to_lowp(c->zlo, W, (long long)M * (lp + lm), prec, s);
-                // FP64 with >= 3 row blocks (33 rows and up): the packed rows k-major, for the kernel that copies both tiles
-                // straight into LDS (below that the G stream bounds the product and the row-major kernel,
-                // with more workgroups per CU, streams it faster)
-                // (FP32: the same, converted to FP32, rows padded to a multiple of 4)
-                const long long ldt = prec == 1 ? (M + 3) / 4 * 4 : (M + 1) / 2 * 2;
-                double* Wt = prec <= 1 ? take(ws, ldt * (lp + lm)) : nullptr;
-                float* Wt32 = prec == 1 ? (float*)take(ws, (ldt * (lp + lm) + 1) / 2) : nullptr;
-                int ltm, lmt;
-                ladder_rows(M, ltm, lmt);
-                const bool kmajor = prec <= 1 && ltm >= 3;
-                if (kmajor) {
-                    k_transpose(W, lp, M, lp, Wt, ldt, s);
-                    k_transpose(W + (long long)M * lp, lm, M, lm, Wt + ldt * lp, ldt, s);
-                    if (prec == 1) k_to_lowp(Wt32, Wt, ldt * (lp + lm), 1, s);
-                }
-                const int eb = prec == 0 ? 8 : prec == 1 ? 4 : 2;
-                const double pk = prec == 0 ? PEAK_FP64_MFMA : prec == 1 ? PEAK_FP32_MFMA : PEAK_BF16_MFMA;
-                for (int blk = 0; blk < 2; ++blk) {
-                    const long long n = blk == 0 ? lp : lm;
-                    if (n == 0) continue;
-                    const long long woff = blk == 0 ? 0 : (long long)M * lp;
-                    double* C = CW + woff;
-                    const double fl = 2.0 * M * (double)n * n;
-                    const double by = eb * (double)n * n + (eb + 8.0) * M * (double)n;
-                    ProfScope p(prec > 0 ? PROF_LADDER_LP : PROF_LADDER, s, fl, by,
-                                1e3 * std::max(fl / pk, by / PEAK_HBM));
-                    if (prec > 0) {
-                        const void* Z = (const char*)c->zlo + woff * eb;
-                        const void* Gl = blk == 0 ? c->Glo : c->Gmlo;
-                        const float* Zt32 = kmajor && prec == 1 ? Wt32 + (blk == 0 ? 0 : ldt * lp) : nullptr;
-                        if (Zt32 && ladder_t32_supported(M, (int)n, (int)n, Zt32, ldt, (const float*)Gl, n) &&
-                            ladder_gemm_t32(M, (int)n, (int)n, 1.0, Zt32, ldt, (const float*)Gl, n, 0.0, C, n,
-                                            ladder_tuned_chunks(4, M, (int)n, (int)n, Zt32, ldt, Gl, n, C, n, c->xb, pe, s),
-                                            c->xb, pe, s)) {
-                            // done on the k-major FP32 kernel
-                        } else if (ladder_lp_supported(prec, M, (int)n, (int)n, Z, n, Gl, n, C, n)) {
-                            const int nch = ladder_tuned_chunks(prec, M, (int)n, (int)n, Z, n, Gl, n, C, n, c->xb, pe, s);
-                            ladder_gemm_lp(prec, M, (int)n, (int)n, 1.0, Z, n, Gl, n, 0.0, C, n, nch, c->xb, pe, s);
-                        } else {
-                            GemmLP g;
-                            g.M = M; g.N = (int)n; g.K = (int)n;
-                            g.A = W + woff; g.sAm = n; g.sAk = 1;
-                            g.B = Gl; g.sBk = n; g.sBn = 1;
-                            g.C = C; g.sCm = n; g.sCn = 1;
-                            gemm_lp(g, prec, s, 1);
-                        }
+                double* V = take(ws, ve);
+                df_ladder(0, M, v, X, c->Bvv, c->zb, c->sb, false, V, ve, s);
+            }
+            ws.release(mk);
+        } else if (dual && !g_dry && ladder_t_supported(M, (int)lp, (int)lp, W, ldt, c->G, lp)) {
+            // both pair blocks in one launch, their partial sums read by k_sigma_fin
+            const double fl = 2.0 * M * ((double)lp * lp + (double)lm * lm);
+            const double by = 8.0 * ((double)lp * lp + (double)lm * lm) + 16.0 * M * (double)(lp + lm);
+            ProfScope p(PROF_LADDER, s, fl, by, 1e3 * std::max(fl / PEAK_FP64_MFMA, by / PEAK_HBM));
+            nl = ladder_t_partials(pr, lm > 0 ? 2 : 1, M, tm, mt, kc, 0x7fffffff, 0, 0, s);
+            Cs = pr[0].P;
+            Cm = pr[1].P;
+        } else {
+            // one launch per block: the row-major FP64 kernel, or the reduced precisions
+            float* Wt32 = prec == 1 ? (float*)take(ws, ((M + 3) / 4 * 4 * (lp + lm) + 1) / 2) : nullptr;
+            if (prec == 1 && kmajor) k_to_lowp(Wt32, W, ldt * (lp + lm), 1, s);
+            else if (prec > 0) k_to_lowp(c->zlo, W, (long long)M * (lp + lm), prec, s);
+            const int eb = prec == 0 ? 8 : prec == 1 ? 4 : 2;
+            const double pk = prec == 0 ? PEAK_FP64_MFMA : prec == 1 ? PEAK_FP32_MFMA : PEAK_BF16_MFMA;
+            for (int blk = 0; blk < 2; ++blk) {
+                const long long n = blk == 0 ? lp : lm;
+                if (n == 0) continue;
+                const long long w0 = blk == 0 ? 0 : woff;
+                double* C = CW + (blk == 0 ? 0 : (long long)M * lp);
+                const double fl = 2.0 * M * (double)n * n;
+                const double by = eb * (double)n * n + (eb + 8.0) * M * (double)n;
+                ProfScope p(prec > 0 ? PROF_LADDER_LP : PROF_LADDER, s, fl, by,
+                            1e3 * std::max(fl / pk, by / PEAK_HBM));
+                if (prec > 0) {
+                    const void* Gl = blk == 0 ? c->Glo : c->Gmlo;
+                    const float* Zt32 = kmajor ? Wt32 + w0 : nullptr;
+                    const void* Z = (const char*)c->zlo + w0 * eb;
+                    if (Zt32 && ladder_t32_supported(M, (int)n, (int)n, Zt32, ldt, (const float*)Gl, n) &&
+                        ladder_gemm_t32(M, (int)n, (int)n, 1.0, Zt32, ldt, (const float*)Gl, n, 0.0, C, n,
+                                        ladder_tuned_chunks(4, M, (int)n, (int)n, Zt32, ldt, Gl, n, C, n, pbuf, pe, s),
+                                        pbuf, pe, s)) {
+                        // done on the k-major FP32 kernel
+                    } else if (!kmajor && ladder_lp_supported(prec, M, (int)n, (int)n, Z, n, Gl, n, C, n)) {
+                        const int nch = ladder_tuned_chunks(prec, M, (int)n, (int)n, Z, n, Gl, n, C, n, pbuf, pe, s);
+                        ladder_gemm_lp(prec, M, (int)n, (int)n, 1.0, Z, n, Gl, n, 0.0, C, n, nch, pbuf, pe, s);
                     } else {
-                        const double* Z = W + woff;
-                        const double* Gb = blk == 0 ? c->G : c->Gm;
-                        const double* Zt = kmajor ? Wt + (blk == 0 ? 0 : ldt * lp) : nullptr;
-                        if (kmajor && ladder_t_supported(M, (int)n, (int)n, Zt, ldt, Gb, n) &&
-                            ladder_gemm_t(M, (int)n, (int)n, 1.0, Zt, ldt, Gb, n, 0.0, C, n,
-                                          ladder_tuned_chunks(3, M, (int)n, (int)n, Zt, ldt, Gb, n, C, n, c->xb, pe, s),
-                                          c->xb, pe, s)) {
-                            // done on the k-major kernel
-                        } else if (ladder_supported(M, (int)n, (int)n, Z, n, Gb, n, C, n)) {
-                            const int nch = ladder_tuned_chunks(0, M, (int)n, (int)n, Z, n, Gb, n, C, n, c->xb, pe, s);
-                            ladder_gemm(M, (int)n, (int)n, 1.0, Z, n, Gb, n, 0.0, C, n, nch, c->xb, pe, s);
-                        } else {
-                            gemm_rm(M, (int)n, (int)n, 1.0, Z, n, false, Gb, n, false, 0.0, C, n, s, 1);
-                        }
+                        GemmLP g;
+                        g.M = M; g.N = (int)n; g.K = (int)n;
+                        g.A = W + w0; g.sAm = kmajor ? 1 : n; g.sAk = kmajor ? ldt : 1;
+                        g.B = Gl; g.sBk = n; g.sBn = 1;
+                        g.C = C; g.sCm = n; g.sCn = 1;
+                        if (!g_dry) gemm_lp(g, prec, s, 1);
+                    }
+                } else {
+                    const double* Z = W + w0;
+                    const double* Gb = blk == 0 ? c->G : c->Gm;
+                    if (kmajor && ladder_t_supported(M, (int)n, (int)n, Z, ldt, Gb, n) &&
+                        ladder_gemm_t(M, (int)n, (int)n, 1.0, Z, ldt, Gb, n, 0.0, C, n,
+                                      ladder_tuned_chunks(3, M, (int)n, (int)n, Z, ldt, Gb, n, C, n, pbuf, pe, s), pbuf, pe,
+                                      s)) {
+                        // done on the k-major kernel
+                    } else if (!kmajor && ladder_supported(M, (int)n, (int)n, Z, n, Gb, n, C, n)) {
+                        const int nch = ladder_tuned_chunks(0, M, (int)n, (int)n, Z, n, Gb, n, C, n, pbuf, pe, s);
+                        ladder_gemm(M, (int)n, (int)n, 1.0, Z, n, Gb, n, 0.0, C, n, nch, pbuf, pe, s);
+                    } else {
+                        Gemm g;
+                        g.M = M; g.N = (int)n; g.K = (int)n;
+                        g.A = Z; g.sAm = kmajor ? 1 : n; g.sAk = kmajor ? ldt : 1;
+                        g.B = Gb; g.sBk = n; g.sBn = 1;
+                        g.C = C; g.sCm = n; g.sCn = 1;
+                        gemm(g, s, 1);
                     }
                 }
-                k_sa_unpack(CW, CW + (long long)M * lp, M, v, c->sb, vv, s);
-                ws.release(mk);
             }
-            // particle-hole terms on the alpha-beta determinants x (z = S + sqrt3 A of x per block):
-            //   d[n][i][a][b] = sum_jd (ib|jd) xt[n][j][a][d] - (ij|bd) x[n][j][a][d] - (ij|ad) x[n][j][d][b]
-            // with rows (n,a) and columns (i,b): the first product through the DF factor,
-            // (Y1 B^T) B with B = Bov as [Q][(j,d)] (its contraction indices j,d sit in one factor), the other
-            // two (both against the same symmetric [(j,d)][(i,b)] matrix P1 = (ij|bd)) as one GEMM over the
-            // stacked rows [Y2; Y3] (the ladder tile streams P1 once per row tile); then
-            // sigma_z += S(d) + sqrt3 A(d)
-            {
-                const int Mph = nv * v, ovi = o * v, X = c->X;
-                double *Y1 = c->xb, *Y2 = c->xtb;
-                double* Y3 = Y2 + (long long)Mph * ovi;  // stacked under Y2 (inside the xtb/sdb region)
-                k_ph_prep(zb, Y1, Y2, Y3, nv, o, v, s);
-                double* D = zb;  // z is not needed any more: the factor product goes here
-                double* E = take(ws, 2 * NVMAX * (long long)o * vv);
-                const long long pe = 2 * NVMAX * (long long)o * vv;
-                double* part = take(ws, pe);
-                double* Wq = take(ws, (long long)NVMAX * v * X);
-                // [Y2; Y3] k-major for the ladder kernel that copies both tiles into LDS, else the row-major tile
-                const long long ldy = 2LL * Mph;
-                double* Yt = take(ws, (long long)ovi * 2 * NVMAX * v);
-                const bool tk = ladder_t_supported(2 * Mph, ovi, ovi, Yt, ldy, c->P1, c->ldm) &&
-                                ladder_t_min_chunks(ovi, ldy, c->ldm) == 1;
-                if (tk) k_transpose(Y2, ovi, 2 * Mph, ovi, Yt, ldy, s);
-                const bool lad = !tk && ladder_supported(2 * Mph, ovi, ovi, Y2, ovi, c->P1, c->ldm, E, ovi);
-                const int nch = tk    ? ladder_tuned_chunks(3, 2 * Mph, ovi, ovi, Yt, ldy, c->P1, c->ldm, E, ovi, part, pe, s)
-                                : lad ? ladder_tuned_chunks(0, 2 * Mph, ovi, ovi, Y2, ovi, c->P1, c->ldm, E, ovi, part, pe, s)
-                                      : 1;
-                {
-                    Gemm g;  // Wq[(n,a)][Q] = sum_(j,d) Y1[(n,a)][(j,d)] Bov[Q][(j,d)]
-                    g.M = Mph; g.N = X; g.K = ovi;
-                    g.A = Y1; g.sAm = ovi; g.sAk = 1;
-                    g.B = c->Bov; g.sBk = 1; g.sBn = ovi;
-                    g.C = Wq; g.sCm = X; g.sCn = 1;
-                    gemm(g, s);
-                }
-                gemm_rm(Mph, ovi, X, 1.0, Wq, X, false, c->Bov, ovi, false, 0.0, D, ovi, s);
-                // (a fixed chunk count may not fit the partial buffer: clamped, as the row-major path does)
-                const int ncht = (int)std::max<long long>(1, std::min<long long>(nch, pe / (2LL * Mph * ovi)));
-                if (tk && ladder_gemm_t(2 * Mph, ovi, ovi, 1.0, Yt, ldy, c->P1, c->ldm, 0.0, E, ovi, ncht, part, pe, s, 2)) {
-                    // done on the k-major kernel
-                } else if (lad) {
-                    ladder_gemm(2 * Mph, ovi, ovi, 1.0, Y2, ovi, c->P1, c->ldm, 0.0, E, ovi, nch, part, pe, s, 2);
-                } else {
-                    gemm_rm(2 * Mph, ovi, ovi, 1.0, Y2, ovi, false, c->P1, c->ldm, false, 0.0, E, ovi, s);
-                }
-                k_ph_fin(c->sb, D, E, E + (long long)Mph * ovi, nv, o, v, s);
-            }
-            // first-order 2p1h terms (ladder + particle-hole), scaled by smx for sm-ADC
-            k_copy2d(ss + v, N, c->sb, ovv, nv, ovv, c->smx, 1.0, s);
+            Cs = CW;
+            Cm = CW + (long long)M * lp;
         }
+        // particle-hole terms
+        gemm_km(ws, X, Mph, ovi, 1.0, c->BovT, c->ldx, Y1t, ldy1, 0.0, Yt, ldy, s);
+        const long long ee = 4LL * NVMAX * o * vv, echunk = 2LL * Mph * ovi;
+        double* E = take(ws, ee);
+        int ne = 1;
+        const int Ke = X + ovi;
+        if (!g_dry && ladder_t_supported(2 * Mph, ovi, Ke, Yt, ldy, c->PB, c->ldm) &&
+            ladder_t_min_chunks(Ke, ldy, c->ldm) == 1) {
+            km_shape(2 * Mph, ovi, Ke, ee, (Ke + 15) / 16 * 16, tm, mt, kc);
+            const LadderTProb pe1{ovi, Ke, Yt, ldy, c->PB, c->ldm, E};
+            ne = ladder_t_partials(&pe1, 1, 2 * Mph, tm, mt, kc, Mph, X, 2, s);
+        } else {
+            gemm_km(ws, 2LL * Mph, ovi, Ke, 1.0, Yt, ldy, c->PB, c->ldm, 0.0, E, ovi, s);
+        }
+        // sigma_z += first-order 2p1h terms (ladder + particle-hole), scaled by smx for sm-ADC
+        k_sigma_fin(ss + v, N, Cs, Cm, nl, c->df ? c->sb : nullptr, E, ne, echunk, nv, o, v, c->smx, s);
     }
 }
 

@@ -243,43 +243,6 @@ __global__ void d_to_z_add_kernel(double* acc, const double* d, long long nblk, 
     }
 }
 
-// Operands of the particle-hole terms, from z (blocks [n][j] of v x v, x = z_S + z_A/sqrt3 per block):
-//   Y2[(n,a)][(j,d)] = x[n][j][a][d],  Y1 = 2 x[n][j][a][d] - x[n][j][d][a],  Y3[(n,a)][(j,d)] = x[n][j][d][a]
-// rows (n,a) of length o*v, so that each term is one GEMM against a symmetric [(j,d)][(i,b)] matrix.
-__global__ void ph_prep_kernel(const double* z, double* Y1, double* Y2, double* Y3, int nv, int o, int v) {
-    const double is3 = 0.57735026918962576451;  // 1/sqrt(3)
-    const int vv = v * v;
-    const long long ov = (long long)o * v;
-    BLOCK_ROWS(blk, (long long)nv * o) BLOCK_COLS(r, vv) {  // blk = n * o + j
-        const int a = r / v, d = r - (r / v) * v;
-        const int n = (int)(blk / o), j = (int)(blk % o);
-        const double zad = z[blk * vv + r], zda = z[blk * vv + d * v + a];
-        const double sy = 0.5 * (zad + zda), an = 0.5 * (zad - zda);
-        const double xad = sy + an * is3, xda = sy - an * is3;
-        const long long out = ((long long)n * v + a) * ov + (long long)j * v + d;
-        Y1[out] = 2.0 * xad - xda;
-        Y2[out] = xad;
-        Y3[out] = xda;
-    }
-}
-
-// acc[n][i][a][b] += S(d) + sqrt3 A(d) over (a,b), d[n][i][a][b] = C12[(n,a)][(i,b)] - C3[(n,b)][(i,a)]
-__global__ void ph_fin_kernel(double* acc, const double* D, const double* E2, const double* E3, int nv, int o, int v) {
-    const double s3 = 1.73205080756887729353;
-    const int vv = v * v;
-    const long long ov = (long long)o * v;
-    BLOCK_ROWS(blk, (long long)nv * o) {  // blk = n * o + i
-        const long long n = blk / o, i = blk % o;
-        BLOCK_COLS(r, vv) {
-            const int a = r / v, b = r - (r / v) * v;
-            const long long ra = (n * v + a) * ov + i * v, rb = (n * v + b) * ov + i * v;
-            const double dab = D[ra + b] - E2[ra + b] - E3[rb + a];
-            const double dba = D[rb + a] - E2[rb + a] - E3[ra + b];
-            acc[blk * vv + r] += 0.5 * (dab + dba) + s3 * 0.5 * (dab - dba);
-        }
-    }
-}
-
 __global__ void k0_add_kernel(double* s2, const double* z, const double* eo, const double* ev, int o, int v,
                               int nvec, long long ld) {
     const int vv = v * v;
@@ -759,22 +722,6 @@ void k_z_to_x(const double* z, double* x, double* xt, long long nblk, int v, hip
     long long n = nblk * v * v;
     if (n <= 0) return;
     hipLaunchKernelGGL(z_to_x_kernel, dim3(nblocks(n)), dim3(NT), 0, s, z, x, xt, nblk, v);
-    LAUNCHCHK();
-}
-void k_ph_prep(const double* z, double* Y1, double* Y2, double* Y3, int nv, int o, int v, hipStream_t s) {
-    if (g_dry) return;
-    long long n = (long long)nv * o * v * v;
-    if (n <= 0) return;
-    hipLaunchKernelGGL(ph_prep_kernel, block_grid((long long)nv * o, (long long)v * v), dim3(NT), 0, s, z, Y1, Y2, Y3, nv,
-                       o, v);
-    LAUNCHCHK();
-}
-void k_ph_fin(double* acc, const double* D, const double* E2, const double* E3, int nv, int o, int v, hipStream_t s) {
-    if (g_dry) return;
-    long long n = (long long)nv * o * v * v;
-    if (n <= 0) return;
-    hipLaunchKernelGGL(ph_fin_kernel, block_grid((long long)nv * o, (long long)v * v), dim3(NT), 0, s, acc, D, E2, E3, nv,
-                       o, v);
     LAUNCHCHK();
 }
 void k_d_to_z_add(double* acc, const double* d, long long nblk, int v, hipStream_t s) {

@@ -282,95 +282,119 @@ __global__ __launch_bounds__(NT) void abt_skinny_kernel(const double* __restrict
 
 // Both 1p <-> 2p1h products of a sigma pass in one stream over U_z [a][k] (a < v <= 256 rows, k < K = o v^2):
 //   part1[c][m][a] = sum over k in chunk c of r2[m][k] U[a][k]      (1p side, summed over chunks afterwards)
-//   out2[m][k]     = sum_a r1[m][a] U[a][k]                          (2p1h side, written directly)
+//   out2[m][k]     = sum_a r1[m][a] U[a][k] + K0[k] r2[m][k]         (2p1h side with its zeroth-order diagonal
+//                                                                    K0 = e_a + e_b - e_i at k = (i,a,b))
 // for m < M <= 16.  A workgroup takes one K chunk; each 16-k slab of U is loaded once, as the MFMA
 // fragments of the 1p product (waves split the 16-row tiles of a, as abt_skinny_kernel does), and
 // parked in LDS; the four waves then read the slab back in the transposed fragment layout (contraction
 // over a, MFMA steps of four a dealt out round-robin to the waves), the four partial 16 x 16 tiles are
 // summed in LDS in wave order and the slab's out2 columns written.  Rows and ks past the ends read as
-// zero.  Requires 16-byte aligned rows (even strides).  U_z in FP32 (the reduced-precision sigma passes) is
-// widened to FP64 on load: the same fragments, and sums in FP64.
+// zero.  VEC: 16-byte loads (aligned rows), else element loads.  U_z in FP32 (the reduced-precision sigma passes)
+// is widened to FP64 on load: the same fragments, and sums in FP64.  (Issuing the next slab's loads before this one's
+// products, with two register sets and so two workgroups a CU, was slower: 445 against 340 us at o=20 v=200, 5
+// vectors.)  FP64 with aligned rows takes couple_lds_kernel below.
+struct CoupleArgs {
+    const void* U; long long ldu;
+    int v;
+    long long K;
+    const double* r2; long long ld2;
+    const double* r1; long long ld1;
+    int M;
+    double* part1;
+    double* out2; long long ldo;
+    const double *eo, *ev;
+};
+
+// 16-byte loads of data aligned to its elements only (odd v)
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
 template <typename TU>
-__global__ __launch_bounds__(NT, 3) void couple_fused_kernel(const TU* __restrict__ U, long long ldu, int v,
-                                                          long long K, long long kc, const double* __restrict__ r2,
-                                                          long long ld2, const double* __restrict__ r1, long long ld1,
-                                                          int M, double* __restrict__ part1, double* __restrict__ out2,
-                                                          long long ldo) {
+__global__ __launch_bounds__(NT, 3) void couple_fused_kernel(CoupleArgs g) {
     extern __shared__ double lds[];
+    const int v = g.v, M = g.M;
     double* Us = lds;                       // [v][17]: the slab, row a, 16 k (+1 pad)
     double* Ps = lds + (long long)v * 17;   // [4][256]: the waves' out2 partial tiles [m][k]
+    double* es = Ps + 1024;                 // [v]: e_a
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r = lane & 15, q = lane >> 4;
-    const long long klo = (long long)blockIdx.x * kc;
-    const long long khi = klo + kc < K ? klo + kc : K;
+    const long long khi = g.K, ks = (long long)gridDim.x * 16;
+    const long long klo = (long long)blockIdx.x * 16;
     const int nt = (v + 15) / 16, nsteps = (v + 3) / 4;
     const bool arow = r < M;
-    const double* Ar = r2 + (arow ? (long long)r * ld2 : 0);
+    const double* Ar = g.r2 + (arow ? (long long)r * g.ld2 : 0);
     const TU* Br[4];
     bool brow[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int a = 16 * (wave + 4 * i) + r;
         brow[i] = a < v;
-        Br[i] = U + (brow[i] ? (long long)a * ldu : 0);
+        Br[i] = (const TU*)g.U + (brow[i] ? (long long)a * g.ldu : 0);
     }
+    for (int a = tid; a < v; a += NT) es[a] = g.ev[a];
     // r1 fragments of this wave's contraction steps s = wave + 4 i: lane (m = r, q) holds r1[m][4 s + q]
     double f1[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const int a = 4 * (wave + 4 * i) + q;
-        f1[i] = (arow && a < v) ? r1[(long long)r * ld1 + a] : 0.0;
+        f1[i] = (arow && a < v) ? g.r1[(long long)r * g.ld1 + a] : 0.0;
     }
     d4 acc[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i] = d4{0.0, 0.0, 0.0, 0.0};
-    for (long long k0 = klo; k0 < khi; k0 += 16) {
+    const int om = tid >> 4, okk = tid & 15;  // this thread's out2 element of a slab
+    struct Slab {
+        double a4[4], b4[4][4], z;
+    };
+    auto load = [&](long long k0, Slab& x) {
         const long long ko = k0 + 4 * q;
-        const bool full = k0 + 16 <= khi;
-        double a4[4], b4[4][4];
-        if (full) {
-            d2 x0 = d2{0.0, 0.0}, x1 = d2{0.0, 0.0};
+        x.z = (om < M && k0 + okk < khi) ? g.r2[(long long)om * g.ld2 + k0 + okk] : 0.0;
+        if (k0 + 16 <= khi) {
+            d2u x0 = d2u{0.0, 0.0}, x1 = d2u{0.0, 0.0};
             if (arow) {
-                x0 = *(const d2*)(Ar + ko);
-                x1 = *(const d2*)(Ar + ko + 2);
+                x0 = *(const d2u*)(Ar + ko);
+                x1 = *(const d2u*)(Ar + ko + 2);
             }
-            a4[0] = x0.x; a4[1] = x0.y; a4[2] = x1.x; a4[3] = x1.y;
+            x.a4[0] = x0.x; x.a4[1] = x0.y; x.a4[2] = x1.x; x.a4[3] = x1.y;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 if constexpr (std::is_same<TU, float>::value) {
                     // FP32 U_z: one 16-byte load of four k, widened to FP64
-                    float4 y = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (wave + 4 * i < nt && brow[i]) y = *(const float4*)(Br[i] + ko);
-                    b4[i][0] = y.x; b4[i][1] = y.y; b4[i][2] = y.z; b4[i][3] = y.w;
+                    f4u y = f4u{0.f, 0.f, 0.f, 0.f};
+                    if (wave + 4 * i < nt && brow[i]) y = *(const f4u*)(Br[i] + ko);
+                    x.b4[i][0] = y.x; x.b4[i][1] = y.y; x.b4[i][2] = y.z; x.b4[i][3] = y.w;
                 } else {
-                    d2 y0 = d2{0.0, 0.0}, y1 = d2{0.0, 0.0};
+                    d2u y0 = d2u{0.0, 0.0}, y1 = d2u{0.0, 0.0};
                     if (wave + 4 * i < nt && brow[i]) {
-                        y0 = *(const d2*)(Br[i] + ko);
-                        y1 = *(const d2*)(Br[i] + ko + 2);
+                        y0 = *(const d2u*)(Br[i] + ko);
+                        y1 = *(const d2u*)(Br[i] + ko + 2);
                     }
-                    b4[i][0] = y0.x; b4[i][1] = y0.y; b4[i][2] = y1.x; b4[i][3] = y1.y;
+                    x.b4[i][0] = y0.x; x.b4[i][1] = y0.y; x.b4[i][2] = y1.x; x.b4[i][3] = y1.y;
                 }
             }
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const long long k = ko + j;
-                a4[j] = (arow && k < khi) ? Ar[k] : 0.0;
+                x.a4[j] = (arow && k < khi) ? Ar[k] : 0.0;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) b4[i][j] = (wave + 4 * i < nt && brow[i] && k < khi) ? Br[i][k] : 0.0;
+                for (int i = 0; i < 4; ++i) x.b4[i][j] = (wave + 4 * i < nt && brow[i] && k < khi) ? Br[i][k] : 0.0;
             }
         }
+    };
+    auto step = [&](long long k0, const Slab& x) {
         // 1p product (k = ko + j at MFMA step j) and the slab into LDS
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (wave + 4 * i >= nt) continue;  // uniform over the wave
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a4[j], b4[i][j], acc[i], 0, 0, 0);
             if (brow[i]) {
-                double* u = Us + (long long)(16 * (wave + 4 * i) + r) * 17 + 4 * q;
+                double* u = Us + (16 * (wave + 4 * i) + r) * 17 + 4 * q;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) u[j] = b4[i][j];
+                for (int j = 0; j < 4; ++j) u[j] = x.b4[i][j];
             }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(x.a4[j], x.b4[i][j], acc[i], 0, 0, 0);
         }
         __syncthreads();
         // 2p1h product over a: D[m][k] += r1[m][a] U[a][k], lane (k = r, a = 4 s + q); the slab's fragments
@@ -395,15 +419,21 @@ __global__ __launch_bounds__(NT, 3) void couple_fused_kernel(const TU* __restric
 #pragma unroll
         for (int e = 0; e < 4; ++e) Ps[wave * 256 + (q + 4 * e) * 16 + r] = d0[e] + d1[e];
         __syncthreads();
-        {
-            const int m = tid >> 4, kk = tid & 15;
-            const long long k = k0 + kk;
-            if (m < M && k < khi)
-                out2[(long long)m * ldo + k] =
-                    ((Ps[m * 16 + kk] + Ps[256 + m * 16 + kk]) + Ps[512 + m * 16 + kk]) + Ps[768 + m * 16 + kk];
+        const long long k = k0 + okk;
+        if (om < M && k < khi) {
+            const unsigned vv = (unsigned)(v * v), ku = (unsigned)k, i = ku / vv, rem = ku - i * vv, a = rem / (unsigned)v,
+                           b = rem - a * (unsigned)v;
+            const double k0e = es[a] + es[b] - g.eo[i];
+            g.out2[(long long)om * g.ldo + k] =
+                (((Ps[tid] + Ps[256 + tid]) + Ps[512 + tid]) + Ps[768 + tid]) + k0e * x.z;
         }
+    };
+    for (long long k0 = klo; k0 < khi; k0 += ks) {
+        Slab x;
+        load(k0, x);
+        step(k0, x);
     }
-    double* P = part1 + (long long)blockIdx.x * M * v;
+    double* P = g.part1 + (long long)blockIdx.x * M * v;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int a = 16 * (wave + 4 * i) + r;
@@ -413,6 +443,169 @@ __global__ __launch_bounds__(NT, 3) void couple_fused_kernel(const TU* __restric
             const int m = q + 4 * e;
             if (m < M) P[(long long)m * v + a] = acc[i][e];
         }
+    }
+}
+
+// The same for FP64 U with 16-byte aligned rows: the slab of U and of r2 goes from HBM straight into LDS by buffer loads
+// one slab ahead (16 bytes a lane, no registers; 8 rows of 128 bytes per instruction), in two buffers, and both products
+// read their fragments from there.  A row's eight 16-byte chunks are stored at slot = chunk ^ ((row / 2) % 8), each lane
+// fetching the chunk that belongs at its slot, so that 16 rows read at one k hit different banks.  Bound by the U_z
+// stream: o=20 v=200, 5 vectors: 335 us with the slab through registers, 315-330 here (4.0 TB/s of the 4.9 that a copy
+// reaches; the slab in flight behind the current one is what bounds it: 540 us at one workgroup a CU).  Slabs are dealt out
+// in turn, so that the chip reads neighbouring columns of each row: 440 us with one contiguous K range per XCD.
+typedef __attribute__((address_space(3))) void* cl_lds_t;
+constexpr unsigned CL_OOR = 0xFFFFFFF0u;
+
+template <int NI>  // v <= 64 NI
+__global__ __launch_bounds__(NT, 2) void couple_lds_kernel(CoupleArgs g) {
+    constexpr int VR = 64 * NI;
+    __shared__ __attribute__((aligned(16))) double U0[VR * 16], U1[VR * 16], Z0[256], Z1[256];
+    __shared__ double Ps[1024], es[VR];
+    const int v = g.v, M = g.M;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, q = lane >> 4;
+    const long long khi = g.K, ks = (long long)gridDim.x * 16;
+    const int nt = (v + 15) / 16, nsteps = (v + 3) / 4;
+    const double* U = (const double*)g.U;
+    for (int a = tid; a < v; a += NT) es[a] = g.ev[a];
+    // rows that no copy writes read as zero
+    for (int t = (v + 7) / 8 * 128 + tid; t < VR * 16; t += NT) U0[t] = U1[t] = 0.0;
+    for (int t = (M > 8 ? 256 : 128) + tid; t < 256; t += NT) Z0[t] = Z1[t] = 0.0;
+    double f1[4 * NI];
+#pragma unroll
+    for (int i = 0; i < 4 * NI; ++i) {
+        const int a = 4 * (wave + 4 * i) + q;
+        f1[i] = (r < M && a < v) ? g.r1[(long long)r * g.ld1 + a] : 0.0;
+    }
+    // copies: group gr = wave + 4 t holds rows 8 gr .. 8 gr + 7; lane l row l / 8 of it, slot l % 8
+    const int lrow = lane >> 3, lslot = lane & 7;
+    const int om = tid >> 4, okk = tid & 15;
+    const unsigned vv = (unsigned)(v * v);
+    double en = 0.0;  // e_i of the thread's element in the slab issued last
+    auto issue = [&](double(&Ub)[VR * 16], double(&Zb)[256], long long k0) {
+#pragma unroll
+        for (int t = 0; t < 2 * NI; ++t) {
+            const int gr = wave + 4 * t, row = 8 * gr + lrow, ch = lslot ^ ((row >> 1) & 7);
+            if (8 * gr >= v) continue;
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                (void*)(U + (long long)8 * gr * g.ldu + k0), (short)0, 0x7fffffff, 0x00020000);
+            const unsigned off = (row < v && k0 + 2 * ch < khi) ? (unsigned)(lrow * (int)g.ldu + 2 * ch) * 8u : CL_OOR;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (cl_lds_t)&Ub[128 * gr], 16, off, 0, 0, 0);
+        }
+        if (8 * wave < M) {
+            const int row = 8 * wave + lrow, ch = lslot ^ ((row >> 1) & 7);
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                (void*)(g.r2 + (long long)8 * wave * g.ld2 + k0), (short)0, 0x7fffffff, 0x00020000);
+            const unsigned off = (row < M && k0 + 2 * ch < khi) ? (unsigned)(lrow * (int)g.ld2 + 2 * ch) * 8u : CL_OOR;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (cl_lds_t)&Zb[128 * wave], 16, off, 0, 0, 0);
+        }
+        en = k0 + okk < khi ? g.eo[(unsigned)(k0 + okk) / vv] : 0.0;
+    };
+    // element k of row x of a tile
+    auto at = [](int x, int k) { return x * 16 + ((((k >> 1) ^ ((x >> 1) & 7)) << 1) | (k & 1)); };
+    d4 acc[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) acc[i] = d4{0.0, 0.0, 0.0, 0.0};
+    // a slab's results are stored after the next slab's loads are issued, so that no wait for loads waits for a store
+    double ov = 0.0;
+    long long ok = khi;
+    auto flush = [&] {
+        if (om < M && ok < khi) g.out2[(long long)om * g.ldo + ok] = ov;
+    };
+    auto step = [&](const double(&Ub)[VR * 16], const double(&Zb)[256], long long k0, double ei) {
+        // 2p1h product over a: lane (k = r, a = 4 s + q), s = wave + 4 i; 1p product: k = 4 j + q at MFMA step j.
+        // Every read ahead of the products; the products past the end are skipped (uniform over the wave).
+        double bb[4 * NI], a4[4], b4[NI][4];
+#pragma unroll
+        for (int i = 0; i < 4 * NI; ++i) bb[i] = Ub[at(4 * (wave + 4 * i) + q, r)];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a4[j] = Zb[at(r, 4 * j + q)];
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) b4[i][j] = Ub[at(16 * (wave + 4 * i) + r, 4 * j + q)];
+        d4 d0 = d4{0.0, 0.0, 0.0, 0.0}, d1 = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < 4 * NI; i += 2) {
+            if (wave + 4 * i >= nsteps) break;
+            d0 = __builtin_amdgcn_mfma_f64_16x16x4f64(f1[i], bb[i], d0, 0, 0, 0);
+            d1 = __builtin_amdgcn_mfma_f64_16x16x4f64(f1[i + 1], bb[i + 1], d1, 0, 0, 0);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) Ps[wave * 256 + (q + 4 * e) * 16 + r] = d0[e] + d1[e];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            if (wave + 4 * i >= nt) break;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a4[j], b4[i][j], acc[i], 0, 0, 0);
+        }
+        // the barrier without the wait on the copies in flight that __syncthreads() would add
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        ok = k0 + okk;
+        if (om < M && ok < khi) {
+            const unsigned rem = (unsigned)ok % vv, a = rem / (unsigned)v, b = rem - a * (unsigned)v;
+            const double k0e = es[a] + es[b] - ei;
+            ov = (((Ps[tid] + Ps[256 + tid]) + Ps[512 + tid]) + Ps[768 + tid]) + k0e * Zb[at(om, okk)];
+        }
+    };
+    auto sync = [] {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+    };
+    long long k0 = (long long)blockIdx.x * 16;
+    if (k0 < khi) issue(U0, Z0, k0);
+    sync();
+    for (; k0 + ks < khi; k0 += 2 * ks) {
+        const double e0 = en;
+        issue(U1, Z1, k0 + ks);
+        flush();
+        step(U0, Z0, k0, e0);
+        sync();
+        const double e1 = en;
+        if (k0 + 2 * ks < khi) issue(U0, Z0, k0 + 2 * ks);
+        flush();
+        step(U1, Z1, k0 + ks, e1);
+        sync();
+    }
+    flush();
+    if (k0 < khi) {
+        step(U0, Z0, k0, en);
+        flush();
+    }
+    double* P = g.part1 + (long long)blockIdx.x * M * v;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const int a = 16 * (wave + 4 * i) + r;
+        if (a >= v) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int m = q + 4 * e;
+            if (m < M) P[(long long)m * v + a] = acc[i][e];
+        }
+    }
+}
+
+// s1[m][a] = sum_c part1[c][m][a] + sum_b M11[a][b] r1[m][b]: 8 outputs per workgroup, chunks and b dealt to 32
+// threads each, summed in order (M11 is symmetric: read along its rows)
+__global__ __launch_bounds__(256) void couple_sum_kernel(const double* part1, int nch, int M, int v, const double* M11,
+                                                         const double* r1, long long ld1, double* s1, long long ld) {
+    const int MN = M * v, t = blockIdx.x * 8 + (threadIdx.x & 7), gq = threadIdx.x >> 3;
+    double acc = 0.0;
+    if (t < MN) {
+        const int m = t / v, a = t - m * v;
+#pragma unroll 8
+        for (int c = gq; c < nch; c += 32) acc += part1[(long long)c * MN + t];
+#pragma unroll 8
+        for (int b = gq; b < v; b += 32) acc += M11[(long long)b * v + a] * r1[(long long)m * ld1 + b];
+    }
+    __shared__ double red[32][9];
+    red[gq][threadIdx.x & 7] = acc;
+    __syncthreads();
+    if (gq == 0 && t < MN) {
+        for (int k = 1; k < 32; ++k) acc += red[k][threadIdx.x];
+        s1[(long long)(t / v) * ld + t % v] = acc;
     }
 }
 
@@ -505,33 +698,39 @@ long long abt_skinny(int M, int N, long long K, const double* A, long long lda, 
 }
 
 template <typename TU>
-static long long couple_fused_t(int M, int v, long long K, const TU* U, long long ldu, const double* r2, long long ld2,
-                                const double* r1, long long ld1, double* out2, long long ldo, double* part1,
-                                long long partial_elems, hipStream_t s) {
-    if (M < 1 || M > 16 || v < 1 || v > 256 || K < 256) return 0;
-    if ((uintptr_t)U % 16 || (uintptr_t)r2 % 16 || ldu % (16 / (long long)sizeof(TU)) || ld2 % 2) return 0;
-    long long want = std::min<long long>(768, K / 256);
-    want = std::min<long long>(want, partial_elems / ((long long)M * v));
-    if (want < 2) return 0;
-    const long long kc = ((K + want - 1) / want + 15) / 16 * 16;
-    const long long nch = (K + kc - 1) / kc;
-    const size_t lds = ((size_t)v * 17 + 4 * 256) * sizeof(double);
-    hipLaunchKernelGGL(couple_fused_kernel<TU>, dim3((unsigned)nch), dim3(NT), lds, s, U, ldu, v, K, kc, r2, ld2, r1,
-                       ld1, M, part1, out2, ldo);
+static bool couple_t(CoupleArgs g, const double* M11, double* s1, long long partial_elems, hipStream_t s) {
+    if (g.M < 1 || g.M > 16 || g.v < 1 || g.v > 256 || g.K < 1 || g.K > 0x7fffffffLL) return false;
+    const bool lds_path = std::is_same<TU, double>::value && (uintptr_t)g.U % 16 == 0 && (uintptr_t)g.r2 % 16 == 0 &&
+                          g.ldu % 2 == 0 && g.ld2 % 2 == 0 && g.ldu < (1LL << 24) && g.ld2 < (1LL << 24);
+    // all workgroups resident at once (two or three a CU); K chunks of at least 64, so that a small U_z spreads over the
+    // chip too
+    long long want = std::min<long long>(lds_path && g.v > 128 ? 512 : 768, (g.K + 63) / 64);
+    want = std::min<long long>(want, partial_elems / ((long long)g.M * g.v));
+    if (want < 1) return false;
+    const long long nch = want;
+    const size_t lds = ((size_t)g.v * 18 + 4 * 256) * sizeof(double);
+    const dim3 grid((unsigned)nch), wg(NT);
+    if (lds_path && g.v <= 64) hipLaunchKernelGGL(couple_lds_kernel<1>, grid, wg, 0, s, g);
+    else if (lds_path && g.v <= 128) hipLaunchKernelGGL(couple_lds_kernel<2>, grid, wg, 0, s, g);
+    else if (lds_path && g.v <= 192) hipLaunchKernelGGL(couple_lds_kernel<3>, grid, wg, 0, s, g);
+    else if (lds_path) hipLaunchKernelGGL(couple_lds_kernel<4>, grid, wg, 0, s, g);
+    else hipLaunchKernelGGL((couple_fused_kernel<TU>), grid, wg, lds, s, g);
+    hipLaunchKernelGGL(couple_sum_kernel, dim3((unsigned)((g.M * g.v + 7) / 8)), dim3(256), 0, s, g.part1, (int)nch, g.M, g.v,
+                       M11, g.r1, g.ld1, s1, g.ldo);
     LAUNCHCHK();
-    return nch;
+    return true;
 }
 
-long long couple_fused(int M, int v, long long K, const double* U, long long ldu, const double* r2, long long ld2,
-                       const double* r1, long long ld1, double* out2, long long ldo, double* part1,
-                       long long partial_elems, hipStream_t s) {
-    return couple_fused_t(M, v, K, U, ldu, r2, ld2, r1, ld1, out2, ldo, part1, partial_elems, s);
-}
-
-long long couple_fused32(int M, int v, long long K, const float* U, long long ldu, const double* r2, long long ld2,
-                         const double* r1, long long ld1, double* out2, long long ldo, double* part1,
-                         long long partial_elems, hipStream_t s) {
-    return couple_fused_t(M, v, K, U, ldu, r2, ld2, r1, ld1, out2, ldo, part1, partial_elems, s);
+bool couple_fused(int M, int v, long long K, const double* U, const float* U32, long long ldu, const double* r, double* out,
+                  long long N, const double* M11, const double* eo, const double* ev, double* part1,
+                  long long partial_elems, hipStream_t s) {
+    CoupleArgs g{};
+    g.U = U32 ? (const void*)U32 : (const void*)U;
+    g.ldu = ldu; g.v = v; g.K = K;
+    g.r2 = r + v; g.ld2 = N; g.r1 = r; g.ld1 = N;
+    g.M = M; g.part1 = part1; g.out2 = out + v; g.ldo = N;
+    g.eo = eo; g.ev = ev;
+    return U32 ? couple_t<float>(g, M11, out, partial_elems, s) : couple_t<double>(g, M11, out, partial_elems, s);
 }
 
 thread_local double* g_gemm_scratch = nullptr;

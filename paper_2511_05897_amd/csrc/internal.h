@@ -84,18 +84,14 @@ struct GemmLP {
 };
 void splitk_reduce(const double* part, int nchunk, int M, int N, double alpha, double beta, double* C,
                    long long sCm, long long sCn, hipStream_t s);
+// the 1p rows and the 1p <-> 2p1h coupling of a sigma pass of M <= 16 vectors r [M][N] = [r1[v], z[K]] (v <= 256),
+// both U_z products in one stream over U [v][K] (or its FP32 copy U32, widened on load): out[m][0..v) = M11 r1 + U z,
+// out[m][v..) = U^T r1 + K0 z; false with nothing launched where the shape or the partial buffer does not fit
+bool couple_fused(int M, int v, long long K, const double* U, const float* U32, long long ldu, const double* r, double* out,
+                  long long N, const double* M11, const double* eo, const double* ev, double* part1,
+                  long long partial_elems, hipStream_t s);
 // part[c][m][n] = sum over K chunk c of A[m][k] B[n][k] for M <= 16, N <= 256 rows contiguous along K (row
 // strides lda, ldb); returns the chunk count (0: nothing launched, shape or partial buffer unsuitable)
-// both U_z products of a sigma pass in one stream over U [v][K] (v <= 256, M <= 16, 16-byte aligned rows):
-// part1[c][m][a] = chunk c's share of sum_k r2[m][k] U[a][k] (sum with splitk_reduce over the returned chunk
-// count), out2[m][k] = sum_a r1[m][a] U[a][k]; returns 0 with nothing launched when the shape does not fit
-long long couple_fused(int M, int v, long long K, const double* U, long long ldu, const double* r2, long long ld2,
-                       const double* r1, long long ld1, double* out2, long long ldo, double* part1,
-                       long long partial_elems, hipStream_t s);
-// the same with U_z in FP32 (widened to FP64 on load; ldu a multiple of 4)
-long long couple_fused32(int M, int v, long long K, const float* U, long long ldu, const double* r2, long long ld2,
-                         const double* r1, long long ld1, double* out2, long long ldo, double* part1,
-                         long long partial_elems, hipStream_t s);
 long long abt_skinny_chunks(int M, int N, long long K, long long partial_elems);
 long long abt_skinny(int M, int N, long long K, const double* A, long long lda, const double* B, long long ldb,
                      double* part, long long partial_elems, hipStream_t s);
@@ -121,6 +117,25 @@ bool ladder_gemm_t(int M, int N, int K, double alpha, const double* Zt, long lon
 void ladder_gemm_t_shape(int M, int N, int K, double alpha, const double* Zt, long long ldz, const double* G,
                          long long ldg, double beta, double* C, long long ldc, int tm, int mtiles, int kc, double* partial,
                          hipStream_t s);
+// one or two k-major products of M rows in one launch, their sums over K chunks of kc left as partial sums
+// P [chunks][M][N]; returns the chunk count.  Row tiles from row_skip on start at k_skip.
+struct LadderTProb {
+    int N, K;
+    const double* Z; long long ldz;
+    const double* G; long long ldg;
+    double* P;
+};
+int ladder_t_partials(const LadderTProb* p, int np, int M, int tm, int mtiles, int kc, int row_skip, int k_skip, int tag,
+                      hipStream_t s);
+// whether that one launch beats the row-major kernel block by block: measured once per shape (the buffers' values do not
+// matter) and kept with the tuner's other choices
+bool ladder_dual_tuned(const LadderTProb* p, int np, int M, int tm, int mtiles, int kc, double* C, double* partial,
+                       long long partial_elems, hipStream_t s);
+// row tiling and K per chunk of the two pair blocks' launch: modelled (km_shape), or ADC3_LADDER_CHUNKS chunks; false if
+// no chunking fits both the 31-bit tile offsets and the partial sums' room
+bool ladder_t_shape(int M, long long lp, long long lm, long long ldz, long long partial, int& tm, int& mt, int& kc);
+// the modelled row tiling and K per chunk (tensor.hip): N columns in all, partial sums of at most partial elements
+void km_shape(long long M, long long N, long long K, long long partial, int kcmax, int& tm, int& mt, int& kc);
 // FP32 operands (FP32 accumulation, FP64 partial sums / output), Z k-major, ldz and ldg multiples of 4
 int ladder_t32_min_chunks(int K, long long ldz, long long ldg);
 bool ladder_t32_supported(int M, int N, int K, const float* Zt, long long ldz, const float* G, long long ldg);
@@ -278,10 +293,12 @@ void k_transpose(const double* src, long long lds, int rows, long long cols, dou
 void k_sa_form(const double* Gf, long long ldf, int a0, int na, int v, double* Gp, double* Gm, hipStream_t s);
 // zero the padding rows of G+ and G-
 void k_sa_zero_pad_rows(double* Gp, double* Gm, int v, hipStream_t s);
-// Y2 = x[n][j][a][d], Y1 = 2x[n][j][a][d] - x[n][j][d][a], Y3 = x[n][j][d][a]
-void k_ph_prep(const double* z, double* Y1, double* Y2, double* Y3, int nv, int o, int v, hipStream_t s);
-// acc[n][i][a][b] += S(d) + sqrt3 A(d), d[n][i][a][b] = D[(n,a)][(i,b)] - E2[(n,a)][(i,b)] - E3[(n,b)][(i,a)]
-void k_ph_fin(double* acc, const double* D, const double* E2, const double* E3, int nv, int o, int v, hipStream_t s);
+// the data passes of a level-3 sigma pass (sigma_passes.hip).  Ws/Wa: packed ladder rows, k-major with rows of ldt, or
+// (ldt 0) row-major, or null; Y0: nrow0 rows of ldy whose second half is zeroed
+void k_sigma_prep(const double* z, long long ldz, int nv, int o, int v, double* Ws, double* Wa, long long ldt, double* Y1,
+                  long long ldy1, double* Y0, int nrow0, double* Y23, long long ldy, hipStream_t s);
+void k_sigma_fin(double* out, long long ldo, const double* Cs, const double* Ca, int nl, const double* L, const double* E,
+                 int ne, long long echunk, int nv, int o, int v, double x1, hipStream_t s);
 // sigma2 += K0 * z, K0[i][a][b] = ev_a + ev_b - eo_i;  z/sigma2 with vector stride ld
 void k_k0_add(double* s2, const double* z, const double* eo, const double* ev, int o, int v, int nvec,
               long long ld, hipStream_t s);

@@ -53,6 +53,8 @@ struct LadderArgs {
     double* P;  // partials [nchunk][M][N] when nchunk > 1
     int M, N, K, Kc, ntn, nchunk;
     double alpha, beta;
+    // k-major kernel: row tiles from row_skip on start at k_skip (rows whose first k_skip elements are zero)
+    int row_skip = 0x7fffffff, k_skip = 0;
 };
 
 // TAG 1 marks the tuner's trial launches, TAG 2 other large GEMMs on this tile (separate symbols
@@ -213,8 +215,12 @@ __device__ inline void block_tile(int nchunk, int ntn, int& chunk, int& nt) {
     }
 }
 
+// One launch may hold two products of the same row count and chunk count (grid z = 2: the ladder's two pair blocks),
+// so that they share the chip's last round.
 template <int TM, int TAG>
-__global__ __launch_bounds__(LNT, 2) void ladder_f64t_kernel(LadderArgs g) {
+__global__ __launch_bounds__(LNT, 2) void ladder_f64t_kernel(LadderArgs g0, LadderArgs g1) {
+    const LadderArgs& g = blockIdx.z ? g1 : g0;
+    if ((int)blockIdx.x >= g.nchunk * g.ntn) return;
     constexpr int BM = 16 * TM, RA = BM + 2, RB = LBN + 2;  // LDS row strides (doubles)
     __shared__ __attribute__((aligned(16))) double As0[LBK][RA], As1[LBK][RA];
     __shared__ __attribute__((aligned(16))) double Bs0[LBK][RB], Bs1[LBK][RB];
@@ -223,7 +229,8 @@ __global__ __launch_bounds__(LNT, 2) void ladder_f64t_kernel(LadderArgs g) {
     int chunk, nt;
     block_tile(g.nchunk, g.ntn, chunk, nt);
     const long long m0 = (long long)blockIdx.y * BM, n0 = (long long)nt * LBN;
-    const int kb = chunk * g.Kc, ke = min(g.K, kb + g.Kc);
+    const int ke = min(g.K, (chunk + 1) * g.Kc);
+    const int kb = min(ke, m0 >= g.row_skip ? max(chunk * g.Kc, g.k_skip) : chunk * g.Kc);
     const __amdgpu_buffer_rsrc_t ra = chunk_rsrc(g.Z + (long long)kb * g.ldz + m0, (long long)(ke - kb) * g.ldz * 8 - m0 * 8);
     const __amdgpu_buffer_rsrc_t rb = chunk_rsrc(g.G + (long long)kb * g.ldg + n0, (long long)(ke - kb) * g.ldg * 8 - n0 * 8);
     // wave w copies rows 4w .. 4w+3 of both tiles; lane l the two elements at column 2l
@@ -276,9 +283,11 @@ __global__ __launch_bounds__(LNT, 2) void ladder_f64t_kernel(LadderArgs g) {
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
     };
-    const int nslab = (ke - kb + LBK - 1) / LBK;
-    issue(As0, Bs0, 0);
-    sync();
+    const int nslab = (ke - kb + LBK - 1) / LBK;  // 0 where the chunk lies before k_skip
+    if (nslab > 0) {
+        issue(As0, Bs0, 0);
+        sync();
+    }
     int s = 0;
     for (; s + 1 < nslab; s += 2) {
         issue(As1, Bs1, s + 1);
@@ -675,21 +684,22 @@ void launch(const LadderArgs& a, int tm, int mtiles, int tag, hipStream_t s) {
 }
 
 template <int TM, int TAG>
-void launch_t_tm(const LadderArgs& a, int mtiles, hipStream_t s) {
-    hipLaunchKernelGGL((ladder_f64t_kernel<TM, TAG>), dim3(a.nchunk * a.ntn, mtiles), dim3(LNT), 0, s, a);
+void launch_t_tm(const LadderArgs& a, const LadderArgs* b, int mtiles, hipStream_t s) {
+    const int gx = std::max(a.nchunk * a.ntn, b ? b->nchunk * b->ntn : 0);
+    hipLaunchKernelGGL((ladder_f64t_kernel<TM, TAG>), dim3(gx, mtiles, b ? 2 : 1), dim3(LNT), 0, s, a, b ? *b : a);
 }
 
 template <int TAG>
-void launch_t_tag(const LadderArgs& a, int tm, int mtiles, hipStream_t s) {
+void launch_t_tag(const LadderArgs& a, const LadderArgs* b, int tm, int mtiles, hipStream_t s) {
     switch (tm) {
-        case 1: launch_t_tm<1, TAG>(a, mtiles, s); break;
-        case 2: launch_t_tm<2, TAG>(a, mtiles, s); break;
-        case 3: launch_t_tm<3, TAG>(a, mtiles, s); break;
-        case 4: launch_t_tm<4, TAG>(a, mtiles, s); break;
-        case 5: launch_t_tm<5, TAG>(a, mtiles, s); break;
-        case 6: launch_t_tm<6, TAG>(a, mtiles, s); break;
-        case 7: launch_t_tm<7, TAG>(a, mtiles, s); break;
-        default: launch_t_tm<8, TAG>(a, mtiles, s); break;
+        case 1: launch_t_tm<1, TAG>(a, b, mtiles, s); break;
+        case 2: launch_t_tm<2, TAG>(a, b, mtiles, s); break;
+        case 3: launch_t_tm<3, TAG>(a, b, mtiles, s); break;
+        case 4: launch_t_tm<4, TAG>(a, b, mtiles, s); break;
+        case 5: launch_t_tm<5, TAG>(a, b, mtiles, s); break;
+        case 6: launch_t_tm<6, TAG>(a, b, mtiles, s); break;
+        case 7: launch_t_tm<7, TAG>(a, b, mtiles, s); break;
+        default: launch_t_tm<8, TAG>(a, b, mtiles, s); break;
     }
 }
 }  // namespace
@@ -836,9 +846,9 @@ bool ladder_gemm_t(int M, int N, int K, double alpha, const double* Zt, long lon
     a.nchunk = (K + a.Kc - 1) / a.Kc;
     a.ntn = (N + LBN - 1) / LBN;
     a.alpha = alpha; a.beta = beta;
-    if (tag == 1) launch_t_tag<1>(a, tm, mtiles, s);
-    else if (tag == 2) launch_t_tag<2>(a, tm, mtiles, s);
-    else launch_t_tag<0>(a, tm, mtiles, s);
+    if (tag == 1) launch_t_tag<1>(a, nullptr, tm, mtiles, s);
+    else if (tag == 2) launch_t_tag<2>(a, nullptr, tm, mtiles, s);
+    else launch_t_tag<0>(a, nullptr, tm, mtiles, s);
     LAUNCHCHK();
     if (a.nchunk > 1) splitk_reduce(partial, a.nchunk, M, N, alpha, beta, C, ldc, 1, s);
     return true;
@@ -854,9 +864,44 @@ void ladder_gemm_t_shape(int M, int N, int K, double alpha, const double* Zt, lo
     a.nchunk = (K + kc - 1) / kc;
     a.ntn = (N + LBN - 1) / LBN;
     a.alpha = alpha; a.beta = beta;
-    launch_t_tag<2>(a, tm, mtiles, s);
+    launch_t_tag<2>(a, nullptr, tm, mtiles, s);
     LAUNCHCHK();
     if (a.nchunk > 1) splitk_reduce(partial, a.nchunk, M, N, alpha, beta, C, ldc, 1, s);
+}
+
+int ladder_t_partials(const LadderTProb* p, int np, int M, int tm, int mtiles, int kc, int row_skip, int k_skip, int tag,
+                      hipStream_t s) {
+    LadderArgs a[2];
+    int nch = 1;
+    for (int i = 0; i < np; ++i) nch = std::max(nch, (p[i].K + kc - 1) / kc);
+    for (int i = 0; i < np; ++i) {
+        a[i].Z = p[i].Z; a[i].ldz = p[i].ldz; a[i].G = p[i].G; a[i].ldg = p[i].ldg;
+        a[i].C = p[i].P; a[i].ldc = p[i].N; a[i].P = p[i].P;
+        a[i].M = M; a[i].N = p[i].N; a[i].K = p[i].K;
+        a[i].Kc = kc; a[i].nchunk = nch;  // (a shorter product's last chunk may be empty: it writes zeros)
+        a[i].ntn = (p[i].N + LBN - 1) / LBN;
+        a[i].alpha = 1.0; a[i].beta = 0.0;
+        a[i].row_skip = row_skip; a[i].k_skip = k_skip;
+    }
+    if (tag == 0) launch_t_tag<0>(a[0], np > 1 ? &a[1] : nullptr, tm, mtiles, s);
+    else if (tag == 1) launch_t_tag<1>(a[0], np > 1 ? &a[1] : nullptr, tm, mtiles, s);
+    else launch_t_tag<2>(a[0], np > 1 ? &a[1] : nullptr, tm, mtiles, s);
+    LAUNCHCHK();
+    return nch;
+}
+
+bool ladder_t_shape(int M, long long lp, long long lm, long long ldz, long long partial, int& tm, int& mt, int& kc) {
+    const int kcmax = (int)std::min<long long>(offset_limit() / (8 * std::max(ldz, lp)) / 64 * 64, (lp + 63) / 64 * 64);
+    if (M <= 0 || kcmax < 64) return false;
+    tm = mt = kc = 0;
+    const char* fixed = std::getenv("ADC3_LADDER_CHUNKS");
+    if (fixed && *fixed) {
+        ladder_rows(M, tm, mt);
+        kc = std::min(kcmax, ladder_chunk_len((int)lp, std::max(1, std::min(std::atoi(fixed), ((int)lp + 255) / 256))));
+    } else {
+        km_shape(M, lp + lm, lp, partial, kcmax, tm, mt, kc);
+    }
+    return kc > 0 && (lp + kc - 1) / kc * M * (lp + lm) <= partial;
 }
 
 int ladder_t32_min_chunks(int K, long long ldz, long long ldg) {
@@ -1073,6 +1118,63 @@ int ladder_tuned_chunks(int prec, int M, int N, int K, const void* Z, long long 
         store_cache(rows_key(key), best_rows);
     }
     return best;
+}
+
+bool ladder_dual_tuned(const LadderTProb* p, int np, int M, int tm, int mtiles, int kc, double* C, double* partial,
+                       long long partial_elems, hipStream_t s) {
+    const int n = p[0].N;
+    const char* fixed = std::getenv("ADC3_LADDER_CHUNKS");
+    if (fixed && *fixed) return true;
+    int nch[2] = {1, 1};
+    for (int i = 0; i < np; ++i) {
+        if (!ladder_supported(M, p[i].N, p[i].K, p[i].Z, p[i].K, p[i].G, p[i].ldg, C, p[i].N)) return true;
+        nch[i] = ladder_tuned_chunks(0, M, p[i].N, p[i].K, p[i].Z, p[i].K, p[i].G, p[i].ldg, C, p[i].N, partial, partial_elems,
+                                     s);
+    }
+    const std::string key = tune_key(0, M, n, n) + " one-launch";
+    auto known = [&](bool& v) {
+        std::lock_guard<std::mutex> lk(g_tune_mu);
+        load_cache();
+        auto it = g_tune.find(key);
+        if (it != g_tune.end()) v = it->second != 0;
+        return it != g_tune.end();
+    };
+    bool one = true;
+    if (known(one)) return one;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return true;
+    std::unique_lock<std::mutex> run_lk(g_tune_run_mu);
+    if (known(one)) return one;
+    struct Events {
+        hipEvent_t e[2] = {};
+        ~Events() {
+            for (hipEvent_t x : e)
+                if (x) (void)hipEventDestroy(x);
+        }
+    } ev;
+    for (hipEvent_t& x : ev.e) HIPCHK(hipEventCreate(&x));
+    float t[2] = {1e30f, 1e30f};
+    for (int round = 0; round < 4; ++round)  // the first untimed
+        for (int w = 0; w < 2; ++w) {
+            HIPCHK(hipEventRecord(ev.e[0], s));
+            if (w) ladder_t_partials(p, np, M, tm, mtiles, kc, 0x7fffffff, 0, 1, s);
+            else
+                for (int i = 0; i < np; ++i)
+                    ladder_run(0, M, p[i].N, p[i].K, p[i].Z, p[i].K, p[i].G, p[i].ldg, C, p[i].N, nch[i], partial,
+                               partial_elems, s);
+            HIPCHK(hipEventRecord(ev.e[1], s));
+            HIPCHK(hipEventSynchronize(ev.e[1]));
+            float ms = 0.f;
+            HIPCHK(hipEventElapsedTime(&ms, ev.e[0], ev.e[1]));
+            if (round > 0) t[w] = std::min(t[w], ms);
+        }
+    one = t[1] <= t[0];
+    {
+        std::lock_guard<std::mutex> lk(g_tune_mu);
+        g_tune[key] = one;
+        store_cache(key, one);
+    }
+    return one;
 }
 
 }  // namespace adc3
