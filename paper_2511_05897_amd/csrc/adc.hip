@@ -1851,31 +1851,24 @@ struct NafCache {
     bool valid = false;
 };
 
-static int naf_blocks(const Blocks& in, double thr, Blocks& out, Arena& ws, hipStream_t s, NafCache* cache = nullptr) {
+// W of one basis, X x X (X <= its leading dimension): the k-major tile wants J_vv with the pair index slow, a transpose of a
+// few tens of MB (o=20 v=200 X=600, 80 kept virtuals: 226 us as a row-major product, about 40 with the transpose).
+static void naf_metric(const Blocks& in, double* W, Arena& ws, hipStream_t s) {
+    const int X = in.X;
+    const long long vv = (long long)in.v * in.v, ldx = X + (X & 1);
+    const size_t mark = ws.mark();
+    double* Jt = take(ws, vv * ldx);
+    k_transpose(in.Bvv, vv, X, vv, Jt, ldx, s);
+    gemm_km(ws, X, X, vv, 1.0, Jt, ldx, Jt, ldx, 0.0, W, X, s);
+    k_symmetrize(W, X, s);
+    ws.release(mark);
+}
+
+// The factor blocks in the natural auxiliary functions N (columns sorted by descending eigenvalue w), kept w >= thr.
+static int naf_project(const Blocks& in, double thr, const double* N, const double* w, Blocks& out, Arena& ws,
+                       hipStream_t s) {
     const int X = in.X, o = in.o, v = in.v;
     const long long vv = (long long)v * v;
-    double* W = take(ws, (long long)X * X);
-    double* w = take(ws, X);
-    double* N = take(ws, (long long)X * X);
-    if (cache && cache->valid) {
-        k_copy(N, cache->N, (long long)X * X, s);
-        k_copy(w, cache->w, X, s);
-    } else {
-        const size_t mark = ws.mark();
-        double* wt = take(ws, X);
-        double* Nt = take(ws, (long long)X * X);
-        double* scr = take(ws, (long long)eig_large_scratch(X));
-        gemm_rm(X, X, (int)vv, 1.0, in.Bvv, vv, false, in.Bvv, vv, true, 0.0, W, X, s);
-        k_symmetrize(W, X, s);
-        eig_large(W, X, w, N, scr, s);
-        k_sort_eig(w, N, X, 1, wt, Nt, s);
-        ws.release(mark);
-        if (cache) {
-            k_copy(cache->N, N, (long long)X * X, s);
-            k_copy(cache->w, w, X, s);
-            cache->valid = !g_dry;
-        }
-    }
     std::vector<double> hw(std::max(X, 1));
     d2h(hw.data(), w, X * sizeof(double), s);
     int xk = 0;
@@ -1892,6 +1885,40 @@ static int naf_blocks(const Blocks& in, double thr, Blocks& out, Arena& ws, hipS
         gemm_rm(xk, (int)vv, X, 1.0, N, X, true, in.Bvv, vv, false, 0.0, out.Bvv, vv, s);
     }
     return xk;
+}
+
+// Sorted eigenvectors N and eigenvalues w of the W of several bases, in one batch (a round of the block solver is bound by
+// latency: five matrices of X = 600 together take as long as one).
+static void naf_eig(const std::vector<const Blocks*>& in, double* N, double* w, Arena& ws, hipStream_t s) {
+    const int nb = (int)in.size(), X = in[0]->X;
+    const long long XX = (long long)X * X;
+    const size_t mark = ws.mark();
+    double* W = take(ws, nb * XX);
+    double* wt = take(ws, X);
+    double* Nt = take(ws, XX);
+    double* scr = take(ws, (long long)eig_batched_scratch(X, nb));
+    for (int b = 0; b < nb; ++b) naf_metric(*in[b], W + b * XX, ws, s);
+    eig_batched(W, X, nb, w, N, scr, s);
+    for (int b = 0; b < nb; ++b) k_sort_eig(w + (long long)b * X, N + b * XX, X, 1, wt, Nt, s);
+    ws.release(mark);
+}
+
+static int naf_blocks(const Blocks& in, double thr, Blocks& out, Arena& ws, hipStream_t s, NafCache* cache = nullptr) {
+    const int X = in.X;
+    double* w = take(ws, X);
+    double* N = take(ws, (long long)X * X);
+    if (cache && cache->valid) {
+        k_copy(N, cache->N, (long long)X * X, s);
+        k_copy(w, cache->w, X, s);
+    } else {
+        naf_eig({&in}, N, w, ws, s);
+        if (cache) {
+            k_copy(cache->N, N, (long long)X * X, s);
+            k_copy(cache->w, w, X, s);
+            cache->valid = !g_dry;
+        }
+    }
+    return naf_project(in, thr, N, w, out, ws, s);
 }
 
 // The ADC(2) 1p block M11 = diag(e) - sym(P), P_ab = sum_klc (2T - T~)_kl^ac (kb|lc), of a basis (the same
@@ -2126,20 +2153,52 @@ static SolveOut solve_impl(Arena& ws, const double* eo, const double* ev, const 
         lockstep_run(jp, s, lockstep_chunk());
         ws.release(mj);
     };
+    // 4c-4e for every basis: its blocks in the kept natural orbitals, then the NAF truncation, the eigenproblems of the bases
+    // that drop virtuals as one batch (the others share one result; a dry run counts all of them in the batch)
+    auto prep_all = [&](std::vector<Blocks>& Bn, std::vector<int>& xks) {
+        GemmScratch gscr(ws, GEMM_SCRATCH);
+        std::vector<Blocks> Bt(nb);
+        std::vector<const Blocks*> own;
+        std::vector<int> slot(nb, -1);
+        for (int b = 0; b < nb; ++b) {
+            if (vks[b] < 1) fail(ADC3_EINVAL, "SS-FNO threshold removes every virtual orbital");
+            transform_blocks(B0, U_all + (long long)b * vv0, vks[b], Bt[b], ws, s);
+            if (naf > 0 && (g_dry || vks[b] != v)) {
+                slot[b] = (int)own.size();
+                own.push_back(&Bt[b]);
+            }
+        }
+        double *N = nullptr, *w = nullptr;
+        if (!own.empty()) {
+            N = take(ws, (long long)own.size() * X * X);
+            w = take(ws, (long long)own.size() * X);
+            naf_eig(own, N, w, ws, s);
+        }
+        for (int b = 0; b < nb; ++b) {
+            Bn[b] = Bt[b];
+            xks[b] = X;
+            if (g_dry && naf > 0) {
+                // the shared result is solved for here, after the projections of the bases before it
+                const size_t m1 = ws.mark();
+                double* N1 = take(ws, (long long)X * X);
+                naf_eig({&Bt[b]}, N1, take(ws, X), ws, s);
+                ws.release(m1);
+            }
+            if (slot[b] >= 0) xks[b] = naf_project(Bt[b], naf, N + (long long)slot[b] * X * X, w + (long long)slot[b] * X, Bn[b], ws, s);
+            else if (naf > 0) xks[b] = naf_blocks(Bt[b], naf, Bn[b], ws, s, &naf_cache);
+            VLOG("basis %d: kept %d virtuals, %d auxiliary functions", b, vks[b], xks[b]);
+        }
+    };
     if (engine == 1) {
         GemmScratch gscr(ws, GEMM_SCRATCH);
         std::vector<Blocks> Bn(nb);
         std::vector<int> xks(nb, X);
         std::vector<long long> Nks(nb);
         std::vector<double*> carried(nb), Y2k(nb);
+        prep_all(Bn, xks);
         for (int b = 0; b < nb; ++b) {
             const int vk = vks[b];
-            if (vk < 1) fail(ADC3_EINVAL, "SS-FNO threshold removes every virtual orbital");
             const double* U = U_all + (long long)b * vv0;
-            Blocks Bt;
-            transform_blocks(B0, U, vk, Bt, ws, s);
-            Bn[b] = Bt;
-            if (naf > 0) xks[b] = naf_blocks(Bt, naf, Bn[b], ws, s, vk == v ? &naf_cache : nullptr);
             const long long Nk = vk + (long long)o * vk * vk;
             if (nroots > Nk) fail(ADC3_EINVAL, "truncated space smaller than nroots");
             Nks[b] = Nk;
@@ -2451,7 +2510,7 @@ static SolveOut solve_impl(Arena& ws, const double* eo, const double* ev, const 
         // basis's context setup overlaps the other bases' Davidsons
         std::vector<Blocks> Bn(nb);
         std::vector<int> xks(nb, X);
-        for (int b = 0; b < nb; ++b) xks[b] = prep_basis(b, Bn[b]);
+        prep_all(Bn, xks);
         std::vector<Arena> sub(nb);
         for (int b = 0; b < nb; ++b) {
             const bool was = g_dry;
