@@ -78,18 +78,25 @@ struct PinnedStage {
     }
 };
 }  // namespace
+// The calling thread's pinned staging buffer (PIN_BYTES, written by copies and, mapped, by kernels; what one left there is
+// read before the next is issued).
+constexpr size_t PIN_BYTES = 1 << 20;
+static double* host_stage() {
+    thread_local PinnedStage pin;
+    if (!pin.p) HIPCHK(hipHostMalloc(&pin.p, PIN_BYTES, hipHostMallocDefault));
+    return (double*)pin.p;
+}
+
 static void d2h(void* dst, const void* src, size_t bytes, hipStream_t s) {
     if (g_dry) {
         std::memset(dst, 0, bytes);
         return;
     }
-    constexpr size_t PIN = 1 << 20;
-    thread_local PinnedStage pin;
-    if (bytes <= PIN) {
-        if (!pin.p) HIPCHK(hipHostMalloc(&pin.p, PIN, hipHostMallocDefault));
-        HIPCHK(hipMemcpyAsync(pin.p, src, bytes, hipMemcpyDeviceToHost, s));
+    if (bytes <= PIN_BYTES) {
+        void* pin = host_stage();
+        HIPCHK(hipMemcpyAsync(pin, src, bytes, hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
-        std::memcpy(dst, pin.p, bytes);
+        std::memcpy(dst, pin, bytes);
         return;
     }
     HIPCHK(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
@@ -851,7 +858,6 @@ static DavResult davidson_impl(Ctx* c, Arena& ws, int nroots, double conv, int m
     double* V = take(ws, (long long)mmax * N);
     double* S = take(ws, (long long)mmax * N);
     double* Xr = take(ws, (long long)nroots * N);
-    double* AX = take(ws, (long long)nroots * N);
     double* R = take(ws, (long long)std::max(nroots, 1) * N);
     double* Gm = take(ws, (long long)mmax * mmax);
     double* Gf = take(ws, (long long)mmax * mmax);  // Gram V S^T, kept incrementally (row stride mmax)
@@ -880,28 +886,39 @@ static DavResult davidson_impl(Ctx* c, Arena& ws, int nroots, double conv, int m
     // ~30% of its length to V or to the block: the second pass restores orthogonality, as in
     // the "twice is enough" rule).  tmp holds nn rows.  Returns the number kept.
     auto orthonormalise = [&](double* Tn, int nn, int m, double* tmp) -> int {
-        k_dots(Tn, N, nn, Tn, N, nn, N, Gw, nn, part, s);
-        k_rscale_rows(Tn, nn, N, Gw, nn, s);
         int acc = nn;
         bool again = true;
+        // up to 16 rows: inner products with V's rows and the block's own (its rows follow V's) in one pass, then
+        // projection and scaling in one
+        bool unit = nn <= 16 && Tn == V + (long long)m * N;
+        if (!unit) {
+            k_dots(Tn, N, nn, Tn, N, nn, N, Gw, nn, part, s);
+            k_rscale_rows(Tn, nn, N, Gw, nn, s);
+        }
         for (int round = 0; round < 3 && acc > 0 && again; ++round) {
-            if (m > 0) {
+            if (unit) {
+                k_dots(V, N, m + acc, Tn, N, acc, N, coef, acc, part, s);
+                k_project(Tn, acc, V, m, N, coef, acc, 1, s);
+                unit = false;
+            } else if (m > 0) {
                 k_dots(V, N, m, Tn, N, acc, N, coef, acc, part, s);
                 k_lincomb(Tn, N, acc, V, N, m, coef, acc, N, -1.0, 1.0, s);
             }
             // Loewdin within the block: T' = (U w^-1/2)^T T over the kept directions
             k_dots(Tn, N, acc, Tn, N, acc, N, Gm, acc, part, s);
-            k_symmetrize(Gm, acc, s);
-            eig_small_sorted(Gm, acc, ev, Y, 1, s);
-            std::vector<double> hq(acc);
-            d2h(hq.data(), ev, acc * sizeof(double), s);
+            double* hq = host_stage();
+            eig_small_gram(Gm, acc, acc, ev, Y, 1, coef, hq, s);
+            HIPCHK(hipStreamSynchronize(s));
             int keep = 0;
             for (int q = 0; q < acc; ++q) keep += (hq[q] > 1e-14 && std::isfinite(hq[q]));
             if (keep == 0) return 0;
             again = hq[keep - 1] < 0.5;  // strong cancellation: orthonormalise once more
-            k_lowdin_coef(coef, Y, ev, acc, keep, s);
-            k_lincomb(tmp, N, keep, Tn, N, acc, coef, keep, N, 1.0, 0.0, s);
-            k_copy(Tn, tmp, (long long)keep * N, s);
+            if (keep <= 16) {
+                k_lincomb(Tn, N, keep, Tn, N, acc, coef, acc, N, 1.0, 0.0, s);  // in place: a thread reads its elements first
+            } else {
+                k_lincomb(tmp, N, keep, Tn, N, acc, coef, acc, N, 1.0, 0.0, s);
+                k_copy(Tn, tmp, (long long)keep * N, s);
+            }
             acc = keep;
         }
         return acc;
@@ -955,34 +972,26 @@ static DavResult davidson_impl(Ctx* c, Arena& ws, int nroots, double conv, int m
     int it_lp = 0;
     sigma_impl(c, ws, V, S, m, s, phase);
     k_dots(V, N, m, S, N, m, N, Gf, mmax, part, s);
-    std::vector<double> thold(nroots, INFINITY), hrn(nroots * nroots + nroots), prev_rn(nroots, INFINITY);
+    std::vector<double> thold(nroots, INFINITY), prev_rn(nroots, INFINITY);
     std::vector<char> mlp_on(nroots, (use_mlp && c->mlp_w) ? 1 : 0);
     std::vector<double> mlp_best(nroots, INFINITY);
     std::vector<int> mlp_stall(nroots, 0);
     if (use_mlp && c->mlp_w) mlp_weights_bf16(c->mlp_w, c->mlp_wb, s);
-    std::vector<double> hY;
     int it = 0;
     for (;;) {
         ++it;
-        // Rayleigh-Ritz on the (incrementally kept) Gram matrix
-        k_copy2d(Gm, m, Gf, mmax, m, m, 1.0, 0.0, s);
-        k_symmetrize(Gm, m, s);
-        eig_small_sorted(Gm, m, ev, Y, 0, s);  // ascending, deterministic signs
-        // Ritz vectors X = Y^T V, AX = Y^T S (first nroots columns of Y)
-        k_copy2d(coef, nroots, Y, m, m, nroots, 1.0, 0.0, s);
-        k_lincomb(Xr, N, nroots, V, N, m, coef, nroots, N, 1.0, 0.0, s);
-        k_lincomb(AX, N, nroots, S, N, m, coef, nroots, N, 1.0, 0.0, s);
-        k_copy(th, ev, nroots, s);
-        k_residual(R, AX, Xr, th, nroots, N, s);
-        k_dots(R, N, nroots, R, N, nroots, N, Gw, nroots, part, s);
-        // the Ritz values travel with the residual Gram: one read-back per iteration
-        k_copy(Gw + (long long)nroots * nroots, ev, nroots, s);
-        d2h(hrn.data(), Gw, (size_t)(nroots * nroots + nroots) * sizeof(double), s);
-        for (int k = 0; k < nroots; ++k) res.w[k] = hrn[(size_t)nroots * nroots + k];
+        // Rayleigh-Ritz on the (incrementally kept) Gram matrix: ascending, deterministic signs
+        eig_small_gram(Gf, mmax, m, ev, Y, 0, nullptr, nullptr, s);
+        // Ritz vectors X = Y^T V and residuals (first nroots columns of Y); the squared norms and the Ritz values are
+        // written to the host, one wait per iteration
+        double* hrn = host_stage();
+        k_ritz(V, S, N, m, Y, m, nroots, ev, Xr, R, part, th, hrn, s);
+        HIPCHK(hipStreamSynchronize(s));
+        for (int k = 0; k < nroots; ++k) res.w[k] = hrn[nroots + k];
         std::vector<int> todo;
         bool finite = true;
         for (int k = 0; k < nroots; ++k) {
-            res.rn[k] = std::sqrt(std::max(0.0, hrn[k * nroots + k]));
+            res.rn[k] = std::isnan(hrn[k]) ? hrn[k] : std::sqrt(hrn[k]);
             if (!std::isfinite(res.w[k]) || !std::isfinite(res.rn[k])) finite = false;
             bool ok = res.rn[k] <= conv && std::fabs(res.w[k] - thold[k]) <= conv;
             if (!ok) todo.push_back(k);
@@ -1097,6 +1106,15 @@ static DavResult davidson_impl(Ctx* c, Arena& ws, int nroots, double conv, int m
         Precond1p p1;
         p1.R = R; p1.T = Tn; p1.N = N; p1.Q = c->m11_Q; p1.w = c->m11_w; p1.th = th; p1.v = c->v;
         const bool p1_batch = c->v <= PRECOND_1P_VMAX;
+        // the diagonal steps of all rows in one launch
+        PrecondRows pd;
+        pd.R = R; pd.T = Tn; pd.D = c->diag; pd.th = th; pd.N = N; pd.off = block1p ? c->v : 0;
+        for (int j = 0; j < nn; ++j) {
+            if (mlp_on[todo[j]]) continue;
+            pd.kidx[pd.nrow] = todo[j];
+            pd.tidx[pd.nrow++] = j;
+        }
+        k_precond_rows(pd, s);
         for (int j = 0; j < nn; ++j) {
             const int k = todo[j];
             if (mlp_on[k]) {
@@ -1119,9 +1137,7 @@ static DavResult davidson_impl(Ctx* c, Arena& ws, int nroots, double conv, int m
                     k_div_shift(y, c->m11_w, th + k, v, s);
                     gemm_rm(1, v, v, 1.0, y, v, false, c->m11_Q, v, true, 0.0, Tn + (long long)j * N, v, s);
                 }
-                k_precond(Tn + (long long)j * N + v, R + (long long)k * N + v, c->diag + v, th + k, 1, N - v, s);
             } else {
-                k_precond(Tn + (long long)j * N, R + (long long)k * N, c->diag, th + k, 1, N, s);
                 if (olsen) {
                     // Olsen: t = (D-theta)^-1 (r - eps x), eps = x.(D-theta)^-1 r / x.(D-theta)^-1 x
                     double* bx = Vk;  // free until the next collapse
@@ -1163,8 +1179,7 @@ static DavResult davidson_impl(Ctx* c, Arena& ws, int nroots, double conv, int m
             if (at > 0 && it >= at && g_nan_at.compare_exchange_strong(at, 0)) k_fill(S + (long long)m * N, N, NAN, s);
         }
         // new Gram columns V[0..m+acc) . S[m..m+acc), mirrored into the new rows
-        k_dots(V, N, m + acc, S + (long long)m * N, N, acc, N, Gf + m, mmax, part, s);
-        k_mirror_cols(Gf, mmax, m, acc, s);
+        k_dots(V, N, m + acc, S + (long long)m * N, N, acc, N, Gf + m, mmax, part, s, m);
         m += acc;
     }
     if (vec_out) k_copy(vec_out, Xr, (long long)nroots * N, s);

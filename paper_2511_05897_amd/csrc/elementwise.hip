@@ -176,6 +176,17 @@ __global__ void precond_kernel(double* T, const double* R, const double* D, cons
     }
 }
 
+__global__ __launch_bounds__(256) void precond_rows_kernel(PrecondRows a) {
+    const int j = blockIdx.y, k = a.kidx[j];
+    const double *r = a.R + k * a.N + a.off, *d = a.D + a.off;
+    const double th = a.th[k];
+    double* t = a.T + a.tidx[j] * a.N + a.off;
+    GRID_STRIDE(i, a.N - a.off) {
+        double den = d[i] - th;
+        if (fabs(den) < 1e-8) den = den < 0 ? -1e-8 : 1e-8;
+        t[i] = r[i] / den;
+    }
+}
 __global__ void rscale_rows_kernel(double* T, int nn, long long n, const double* G, int ldg) {
     long long tot = (long long)nn * n;
     GRID_STRIDE(t, tot) {
@@ -183,13 +194,6 @@ __global__ void rscale_rows_kernel(double* T, int nn, long long n, const double*
         double g = G[(long long)j * ldg + j];
         T[t] = (g > 0.0) ? T[t] / sqrt(g) : 0.0;
     }
-}
-
-__global__ void lowdin_coef_kernel(double* coef, const double* U, const double* w, int acc, int keep) {
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= acc * keep) return;
-    int j = t / keep, q = t % keep;
-    coef[t] = U[j * acc + q] / sqrt(w[q]);
 }
 
 __global__ void scale_vec_kernel(double* x, long long n, const double* f) {
@@ -690,6 +694,11 @@ void k_precond(double* T, const double* R, const double* D, const double* th, in
     hipLaunchKernelGGL(precond_kernel, dim3(nblocks(t)), dim3(NT), 0, s, T, R, D, th, nk, n);
     LAUNCHCHK();
 }
+void k_precond_rows(const PrecondRows& a, hipStream_t s) {
+    if (g_dry || a.nrow <= 0 || a.N <= a.off) return;
+    hipLaunchKernelGGL(precond_rows_kernel, dim3(std::min(nblocks(a.N - a.off), 1024u), a.nrow), dim3(256), 0, s, a);
+    LAUNCHCHK();
+}
 void k_scale_vec(double* x, long long n, const double* f, hipStream_t s) {
     if (g_dry) return;
     if (n <= 0) return;
@@ -701,12 +710,6 @@ void k_rscale_rows(double* T, int nn, long long n, const double* G, int ldg, hip
     long long t = (long long)nn * n;
     if (t <= 0) return;
     hipLaunchKernelGGL(rscale_rows_kernel, dim3(nblocks(t)), dim3(NT), 0, s, T, nn, n, G, ldg);
-    LAUNCHCHK();
-}
-void k_lowdin_coef(double* coef, const double* U, const double* w, int acc, int keep, hipStream_t s) {
-    if (g_dry) return;
-    if (acc <= 0 || keep <= 0) return;
-    hipLaunchKernelGGL(lowdin_coef_kernel, dim3((acc * keep + 255) / 256), dim3(256), 0, s, coef, U, w, acc, keep);
     LAUNCHCHK();
 }
 void k_check_B(const double* B, int X, int n, double* flags, hipStream_t s) {

@@ -234,6 +234,14 @@ void k_colsign(double* A, long long lda, int rows, int cols, hipStream_t s);
 void k_residual(double* R, const double* AX, const double* X, const double* theta, int nk, long long n, hipStream_t s);
 // T[k][i] = R[k][i] / (D[i] - theta[k]) with |D - theta| >= floor
 void k_precond(double* T, const double* R, const double* D, const double* theta, int nk, long long n, hipStream_t s);
+// the same for up to 40 rows: T[tidx[j]][off ..] from R[kidx[j]][off ..], theta[kidx[j]], rows of N
+struct PrecondRows {
+    const double *R = nullptr, *D = nullptr, *th = nullptr;
+    double* T = nullptr;
+    long long N = 0, off = 0;
+    int nrow = 0, kidx[40], tidx[40];
+};
+void k_precond_rows(const PrecondRows& a, hipStream_t s);
 void k_olsen(double* T, const double* B, const double* sc, long long n, hipStream_t s);  // T -= (sc[0]/sc[1]) B
 void k_div_shift(double* y, const double* lam, const double* th, int n, hipStream_t s);  // y /= lam - th[0]
 // exact 1p-block preconditioner step of nrow <= 16 vectors:
@@ -250,8 +258,6 @@ void k_precond_1p(const Precond1p& a, hipStream_t s);
 void k_scale_vec(double* x, long long n, const double* factor_dev, hipStream_t s);   // x *= factor[0]
 // row j of T[nn][n] *= 1/sqrt(G[j*ldg + j])  (rows with G <= 0 are zeroed)
 void k_rscale_rows(double* T, int nn, long long n, const double* G, int ldg, hipStream_t s);
-// coef[j*keep + q] = U[j*acc + q] / sqrt(w[q]),  j < acc, q < keep
-void k_lowdin_coef(double* coef, const double* U, const double* w, int acc, int keep, hipStream_t s);
 // fixed-shape block Davidson helpers (no host decisions):
 // G[m][m]: rows/columns of directions with valid[j] == 0 zeroed, their diagonal set above the valid
 // block's Gershgorin bound; cnt[0] = number of valid directions
@@ -314,10 +320,17 @@ void k_diag_adc(double* diag, const double* M11, const double* eo, const double*
 // ---------------------------------------------------------------------------
 // reductions (deterministic, FP64)
 // ---------------------------------------------------------------------------
-// G[p][q] = sum_i X[p*ldx + i] * Y[q*ldy + i], p < np, q < nq  (G row stride ldg)
+// G[p][q] = sum_i X[p*ldx + i] * Y[q*ldy + i], p < np, q < nq  (G row stride ldg).  mirror = m0 >= 0: G is the columns from
+// m0 on of a symmetric matrix (X's rows from m0 on pair with Y's), whose mirrored rows are written too
 void k_dots(const double* X, long long ldx, int np, const double* Y, long long ldy, int nq, long long n,
-            double* G, int ldg, double* partial, hipStream_t s);
+            double* G, int ldg, double* partial, hipStream_t s, int mirror = -1);
 size_t dots_partial_elems(int np, int nq, long long n);
+// X = Y^T V, R = Y^T S - ev X for nr roots over the m rows of V and S; host[k] = |R_k|^2, host[nr + k] = th[k] = ev[k] (host:
+// memory of the host that the device writes).  part: dots_partial_elems(m, m, n)
+void k_ritz(const double* V, const double* S, long long n, int m, const double* Y, int ldy, int nr, const double* ev,
+            double* X, double* R, double* part, double* th, double* host, hipStream_t s);
+// T[q] = f_q (T[q] - sum_p C[p][q] V[p]) for nq <= 16 rows, f_q = 1/sqrt(C[m + q][q]) if scale, else 1
+void k_project(double* T, int nq, const double* V, int m, long long n, const double* C, int ldc, int scale, hipStream_t s);
 // Y[q][i] = beta*Y[q][i] + alpha * sum_p C[p*ldc + q] * X[p][i]    (linear combination of rows)
 void k_lincomb(double* Y, long long ldy, int nq, const double* X, long long ldx, int np, const double* C,
                int ldc, long long n, double alpha, double beta, hipStream_t s);
@@ -328,6 +341,10 @@ void k_lincomb(double* Y, long long ldy, int nq, const double* X, long long ldx,
 // A[n][n] -> w[n], V[n][n] columns eigenvectors (row-major V[i*n+k])
 // n <= 96, one workgroup, A kept; sorted ascending (desc 0) or descending, signs as k_sort_eig
 void eig_small_sorted(const double* A, int n, double* w, double* V, int desc, hipStream_t s);
+// the same of (A + A^T)/2, rows of lda; host (nullable): a copy of w in host memory the device writes; coef (nullable):
+// V w^-1/2, columns as V, zero where w <= 0
+void eig_small_gram(const double* A, int lda, int n, double* w, double* V, int desc, double* coef, double* host,
+                    hipStream_t s);
 // any n, A destroyed, pairs unsorted
 void eig_large(double* A, int n, double* w, double* V, double* scratch, hipStream_t s);
 size_t eig_large_scratch(int n);

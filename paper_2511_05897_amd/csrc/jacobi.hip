@@ -181,9 +181,11 @@ inline int small_threads(int n) {
 }
 
 // One workgroup per matrix A[blockIdx.x][n][n].  desc < 0: eigenpairs as the solver leaves them; 0 / 1: sorted
-// ascending / descending (ties by position), each vector's largest |.| entry positive (the first of equals).
+// ascending / descending (ties by position), each vector's largest |.| entry positive (the first of equals).  A's rows
+// lda apart, (A + A^T)/2 if sym; sorted: also w to host and V w^-1/2 to coef where given.
 template <int NTH>
-__global__ __launch_bounds__(NTH) void jacobi_small_kernel(const double* Ag, int n, double* w, double* Vg, int desc) {
+__global__ __launch_bounds__(NTH) void jacobi_small_kernel(const double* Ag, int lda, int sym, int n, double* w, double* Vg,
+                                                           int desc, double* coef, double* host) {
     extern __shared__ double sm[];
     __shared__ int rank[SMALL_MAX];
     __shared__ double sgn[SMALL_MAX], ww[SMALL_MAX];
@@ -192,12 +194,14 @@ __global__ __launch_bounds__(NTH) void jacobi_small_kernel(const double* Ag, int
     double* V = sm + (size_t)np * ld;
     const int tid = threadIdx.x;
     const long long nn = (long long)n * n;
-    Ag += blockIdx.x * nn;
+    Ag += (long long)blockIdx.x * n * lda;
     Vg += blockIdx.x * nn;
     w += (long long)blockIdx.x * n;
     for (int t = tid; t < np * np; t += NTH) {
         const int i = t / np, j = t - (t / np) * np;
-        A[i * ld + j] = (i < n && j < n) ? Ag[i * n + j] : 0.0;  // odd n: a zero row and column, never rotated
+        double a = (i < n && j < n) ? Ag[i * lda + j] : 0.0;
+        if (sym && i < n && j < n) a = 0.5 * (a + Ag[j * lda + i]);
+        A[i * ld + j] = a;  // odd n: a zero row and column, never rotated
         if (i < n) V[i * ld + j] = (i == j) ? 1.0 : 0.0;
     }
     __syncthreads();
@@ -225,11 +229,14 @@ __global__ __launch_bounds__(NTH) void jacobi_small_kernel(const double* Ag, int
         rank[tid] = rk;
         sgn[tid] = sg;
         w[rk] = wi;
+        if (host) host[rk] = wi;
     }
     __syncthreads();
     for (int t = tid; t < n * n; t += NTH) {
         const int i = t / n, j = t - (t / n) * n;
-        Vg[i * n + rank[j]] = sgn[j] * V[i * ld + j];
+        const double x = sgn[j] * V[i * ld + j];
+        Vg[i * n + rank[j]] = x;
+        if (coef) coef[i * n + rank[j]] = ww[j] > 0.0 ? x / sqrt(ww[j]) : 0.0;
     }
 }
 
@@ -577,23 +584,32 @@ static void small_attr() {
     (void)set;
 }
 
-static void eig_small_batch(const double* A, int n, int nb, double* w, double* V, int desc, hipStream_t s) {
+static void eig_small_batch(const double* A, int lda, int sym, int n, int nb, double* w, double* V, int desc, double* coef,
+                            double* host, hipStream_t s) {
     if (g_dry) return;
     if (n <= 0 || nb <= 0) return;
     if (n > SMALL_MAX) fail(-1, "eig_small: n too large");
     small_attr();
     const int np = n + (n & 1);
     const size_t lds = 2 * (size_t)np * (np + 1) * sizeof(double);
+    auto go = [&](auto kern, int nth) {
+        hipLaunchKernelGGL(kern, dim3(nb), dim3(nth), lds, s, A, lda, sym, n, w, V, desc, coef, host);
+    };
     switch (small_threads(n)) {
-        case 256: hipLaunchKernelGGL(jacobi_small_kernel<256>, dim3(nb), dim3(256), lds, s, A, n, w, V, desc); break;
-        case 512: hipLaunchKernelGGL(jacobi_small_kernel<512>, dim3(nb), dim3(512), lds, s, A, n, w, V, desc); break;
-        default: hipLaunchKernelGGL(jacobi_small_kernel<1024>, dim3(nb), dim3(1024), lds, s, A, n, w, V, desc);
+        case 256: go(jacobi_small_kernel<256>, 256); break;
+        case 512: go(jacobi_small_kernel<512>, 512); break;
+        default: go(jacobi_small_kernel<1024>, 1024);
     }
     LAUNCHCHK();
 }
 
 void eig_small_sorted(const double* A, int n, double* w, double* V, int desc, hipStream_t s) {
-    eig_small_batch(A, n, 1, w, V, desc ? 1 : 0, s);
+    eig_small_batch(A, n, 0, n, 1, w, V, desc ? 1 : 0, nullptr, nullptr, s);
+}
+
+void eig_small_gram(const double* A, int lda, int n, double* w, double* V, int desc, double* coef, double* host,
+                    hipStream_t s) {
+    eig_small_batch(A, lda, 1, n, 1, w, V, desc ? 1 : 0, coef, host, s);
 }
 
 namespace {
@@ -671,7 +687,7 @@ void eig_batched(double* A, int n, int nb, double* w, double* V, double* scratch
     ProfScope prof(PROF_EIG, s, 0.0, 0.0);
     if (n <= 0 || nb <= 0) return;
     if (n <= SMALL_MAX) {
-        eig_small_batch(A, n, nb, w, V, -1, s);
+        eig_small_batch(A, n, 0, n, nb, w, V, -1, nullptr, nullptr, s);
         return;
     }
     eig_block(A, n, nb, w, V, scratch, s);

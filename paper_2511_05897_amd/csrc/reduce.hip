@@ -13,9 +13,11 @@ namespace adc3 {
 namespace {
 inline long long chunk_of(long long n) { return std::max<long long>(256, (n + 8191) / 8192); }
 
-// G[p*ldg + q] = sum_c partial[c][r][s] with (r,s) = (p,q) or (q,p) when swapped
+// G[p*ldg + q] = sum_c partial[c][r][s] with (r,s) = (p,q) or (q,p) when swapped.  m0 >= 0: G is the block of columns
+// m0 .. of a symmetric matrix (G = matrix + m0): the element goes to its mirrored place too, and of the block's own square
+// (rows m0 ..) the upper half counts.
 __global__ void sum_partials_kernel(const double* partial, long long nchunk, int M, int N, int swapped, double* G,
-                                    int ldg) {
+                                    int ldg, int m0) {
     const int t = blockIdx.x;  // output element of the partial [M][N] block
     const long long MN = (long long)M * N;
     double acc = 0.0;
@@ -27,8 +29,10 @@ __global__ void sum_partials_kernel(const double* partial, long long nchunk, int
     if (threadIdx.x == 0) {
         double s = red[0] + red[1] + red[2] + red[3];
         int r = t / N, q = t % N;
-        if (swapped) G[(long long)q * ldg + r] = s;
-        else G[(long long)r * ldg + q] = s;
+        const int i = swapped ? q : r, j = swapped ? r : q;
+        if (m0 >= 0 && i - m0 > j) return;
+        G[(long long)i * ldg + j] = s;
+        if (m0 >= 0) G[(long long)(m0 + j) * ldg + i - m0] = s;
     }
 }
 // Small Gram blocks (at most 64 products, e.g. residual norms and the Gram of a new block): one pass on the vector ALUs,
@@ -147,6 +151,118 @@ __global__ __launch_bounds__(256) void lincomb_kernel(double* Y, long long ldy, 
     }
 }
 
+// Rayleigh-Ritz vectors and residuals of nq <= NQ roots in one pass over V and S (rows 0..m-1 of n):
+//   X[q] = sum_p Y[p][q] V[p],   R[q] = sum_p Y[p][q] S[p] - th[q] X[q],   part[block][q] = partial |R[q]|^2
+// bound by the stream of V and S (o=16 v=120, 5 roots, m = 30: 27 us for 0.13 GB, 55 as
+// two products, a residual pass and a Gram).
+template <int NQ>
+__global__ __launch_bounds__(256) void ritz_kernel(const double* V, const double* S, long long n, int m, const double* Y,
+                                                   int ldy, int nq, const double* th, double* X, double* R, double* part,
+                                                   int ldp) {
+    double nrm[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) nrm[q] = 0.0;
+    for (long long t = 2 * ((long long)blockIdx.x * 256 + threadIdx.x); t < n; t += 512LL * gridDim.x) {
+        const bool two = t + 1 < n;
+        auto ld = [&](const double* p) {
+            if (two) return *(const d2v*)p;
+            return d2v{*p, 0.0};
+        };
+        d2v x[NQ], ax[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) x[q] = ax[q] = d2v{0.0, 0.0};
+#pragma unroll 4
+        for (int p = 0; p < m; ++p) {
+            const d2v a = ld(V + p * n + t), b = ld(S + p * n + t);
+            const double* c = Y + (long long)p * ldy;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const double y = q < nq ? c[q] : 0.0;
+                x[q] += y * a;
+                ax[q] += y * b;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            if (q >= nq) break;
+            const d2v r = ax[q] - th[q] * x[q];
+            nrm[q] += r.x * r.x + r.y * r.y;
+            double *xo = X + q * n + t, *ro = R + q * n + t;
+            if (two) {
+                *(d2v*)xo = x[q];
+                *(d2v*)ro = r;
+            } else {
+                *xo = x[q].x;
+                *ro = r.x;
+            }
+        }
+    }
+    __shared__ double red[4][NQ];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    wave_halve<32, NQ>(nrm, lane);
+    constexpr int L = 64 / NQ;
+    if (lane % L == 0) red[wave][lane / L] = nrm[0];
+    __syncthreads();
+    const int q = threadIdx.x;
+    if (q < nq) part[(long long)blockIdx.x * ldp + q] = ((red[0][q] + red[1][q]) + red[2][q]) + red[3][q];
+}
+
+// host[q] = sum_b part[b][q], host[nr + q] = ev[q] (host memory the device can write), th[q] = ev[q]
+__global__ __launch_bounds__(256) void ritz_norms_kernel(const double* part, int nb, int nr, const double* ev, double* th,
+                                                         double* host) {
+    const int q = blockIdx.x;
+    double acc = 0.0;
+    for (int b = threadIdx.x; b < nb; b += 256) acc += part[(long long)b * nr + q];
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
+    __shared__ double red[4];
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        host[q] = red[0] + red[1] + red[2] + red[3];
+        host[nr + q] = ev[q];
+        th[q] = ev[q];
+    }
+}
+
+// T[q] = f_q (T[q] - sum_p C[p][q] V[p]) for nq <= NQ rows, f_q = 1 / sqrt(C[m + q][q]) (0 where that is not positive) if
+// scale, else 1: new directions brought to unit length and projected against V in one pass, C holding the inner
+// products with V's rows and, below them, with the directions themselves.
+template <int NQ>
+__global__ __launch_bounds__(256) void project_kernel(double* T, const double* V, long long n, int m, const double* C,
+                                                      int ldc, int nq, int scale) {
+    double f[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const double g = scale && q < nq ? C[(long long)(m + q) * ldc + q] : 1.0;
+        f[q] = g > 0.0 ? 1.0 / sqrt(g) : 0.0;
+    }
+    for (long long t = 2 * ((long long)blockIdx.x * 256 + threadIdx.x); t < n; t += 512LL * gridDim.x) {
+        const bool two = t + 1 < n;
+        auto ld = [&](const double* p) {
+            if (two) return *(const d2v*)p;
+            return d2v{*p, 0.0};
+        };
+        d2v x[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) x[q] = q < nq ? ld(T + q * n + t) : d2v{0.0, 0.0};
+#pragma unroll 4
+        for (int p = 0; p < m; ++p) {
+            const d2v a = ld(V + p * n + t);
+            const double* c = C + (long long)p * ldc;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) x[q] -= (q < nq ? c[q] : 0.0) * a;
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            if (q >= nq) break;
+            const d2v y = f[q] > 0.0 ? f[q] * x[q] : d2v{0.0, 0.0};
+            double* o = T + q * n + t;
+            if (two) *(d2v*)o = y;
+            else *o = y.x;
+        }
+    }
+}
+
 template <int NQ>
 void launch_lincomb(double* Y, long long ldy, int nq, const double* X, long long ldx, int np, const double* C, int ldc,
                     long long n, double alpha, double beta, hipStream_t s) {
@@ -175,7 +291,7 @@ size_t dots_partial_elems(int np, int nq, long long n) {
 }
 
 void k_dots(const double* X, long long ldx, int np, const double* Y, long long ldy, int nq, long long n, double* G,
-            int ldg, double* partial, hipStream_t s) {
+            int ldg, double* partial, hipStream_t s, int mirror) {
     if (g_dry) return;
     if (np <= 0 || nq <= 0) return;
     // rows of the GEMM = the smaller set (skinny tiles when it is <= 16)
@@ -200,7 +316,7 @@ void k_dots(const double* X, long long ldx, int np, const double* Y, long long l
             LAUNCHCHK();
             // partial[c][r][m] with r over the N operand: the transposed block of the GEMM's layout
             hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)MN), dim3(256), 0, s, partial, nch, N, M,
-                               swapped ? 0 : 1, G, ldg);
+                               swapped ? 0 : 1, G, ldg, mirror);
             LAUNCHCHK();
             return;
         }
@@ -210,7 +326,7 @@ void k_dots(const double* X, long long ldx, int np, const double* Y, long long l
         const long long nch = abt_skinny(M, N, n, A, lda, B, ldb, partial, (long long)dots_partial_elems(np, nq, n), s);
         if (nch > 0) {
             hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)MN), dim3(256), 0, s, partial, nch, M, N,
-                               swapped ? 1 : 0, G, ldg);
+                               swapped ? 1 : 0, G, ldg, mirror);
             LAUNCHCHK();
             return;
         }
@@ -232,7 +348,39 @@ void k_dots(const double* X, long long ldx, int np, const double* Y, long long l
         gemm(g, s);
     }
     hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)MN), dim3(256), 0, s, partial, nchunk, M, N,
-                       swapped ? 1 : 0, G, ldg);
+                       swapped ? 1 : 0, G, ldg, mirror);
+    LAUNCHCHK();
+}
+
+void k_ritz(const double* V, const double* S, long long n, int m, const double* Y, int ldy, int nr, const double* ev,
+           double* X, double* R, double* part, double* th, double* host, hipStream_t s) {
+    if (g_dry || nr <= 0 || n <= 0) return;
+    const int nb = (int)std::min<long long>(2048, (n + 511) / 512);
+    for (int q0 = 0; q0 < nr; q0 += 8) {
+        const int nq = std::min(8, nr - q0);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, s, V, S, n, m, Y + q0, ldy, nq, ev + q0, X + q0 * n, R + q0 * n,
+                               part + q0, nr);
+        };
+        if (nq <= 1) go(ritz_kernel<1>);
+        else if (nq <= 2) go(ritz_kernel<2>);
+        else if (nq <= 4) go(ritz_kernel<4>);
+        else go(ritz_kernel<8>);
+    }
+    hipLaunchKernelGGL(ritz_norms_kernel, dim3(nr), dim3(256), 0, s, part, nb, nr, ev, th, host);
+    LAUNCHCHK();
+}
+
+void k_project(double* T, int nq, const double* V, int m, long long n, const double* C, int ldc, int scale, hipStream_t s) {
+    if (g_dry || nq <= 0 || n <= 0) return;
+    if (nq > 16) fail(-1, "k_project: more than 16 rows");
+    const int nb = (int)std::min<long long>(4096, (n + 511) / 512);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, s, T, V, n, m, C, ldc, nq, scale); };
+    if (nq <= 1) go(project_kernel<1>);
+    else if (nq <= 2) go(project_kernel<2>);
+    else if (nq <= 4) go(project_kernel<4>);
+    else if (nq <= 8) go(project_kernel<8>);
+    else go(project_kernel<16>);
     LAUNCHCHK();
 }
 

@@ -25,7 +25,10 @@ __device__ inline long long qidx(int a, int b, int v) {  // a < b
 }
 
 // A workgroup takes the tile pair (tc <= td) of 16 x 16 elements for 16 rows m = (n, j): 128-byte runs on every side
-// (along d and c of z, along c and d of the operands' columns, along m of the k-major packed rows).
+// (along d and c of z, along c and d of the operands' columns, along m of the k-major packed rows).  16 waves a workgroup:
+// a small sigma has few tile pairs and waits for each (one vector of o=16 v=120, 37 workgroups: 26 us with four waves,
+// 9.3
+// with 16; five of o=20 v=200: 42 and @@P2@@).
 constexpr int PT = 16, PR = 17, PM = PT * PR + 1;  // tile, LDS row stride, stride between rows m
 
 struct SigmaPrep {
@@ -38,25 +41,25 @@ struct SigmaPrep {
     double* Y0; int nrow0;           // nrow0 rows of ldy before Y23: the second half (columns nv v ..) is zeroed
 };
 
-__global__ __launch_bounds__(256) void sigma_prep_kernel(SigmaPrep g) {
+__global__ __launch_bounds__(1024) void sigma_prep_kernel(SigmaPrep g) {
     __shared__ double A[PT * PM], B[PT * PM];
     const int v = g.v, o = g.o, M = g.nv * o, vv = v * v;
     const int nt = (v + PT - 1) / PT, npr = nt * (nt + 1) / 2;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int m0 = blockIdx.y * PT, mn = min(PT, M - m0);
+    const int tx = threadIdx.x & 15, ty = (threadIdx.x >> 4) & 15, tz = threadIdx.x >> 8;  // tz: four rows m at a time
+    const int m0 = blockIdx.y * PT, mn = min(PT, M - m0), half = g.nv * v;
+    // the zero half of the rows before Y23, dealt to the whole grid
+    for (int r = blockIdx.y * gridDim.x + blockIdx.x; r < g.nrow0; r += gridDim.x * gridDim.y)
+        for (int c = threadIdx.x; c < half; c += 1024) g.Y0[r * g.ldy + half + c] = 0.0;
     if ((int)blockIdx.x == npr) {
-        // padding of the packed rows (pairs np .. lp, nm .. lm) and the zero half of the rows before Y23
+        // padding of the packed rows (pairs np .. lp, nm .. lm)
         const long long np = (long long)v * (v + 1) / 2, nm = (long long)v * (v - 1) / 2;
         if (g.Ws) {
-            for (int t = threadIdx.x; t < 8 * mn; t += 256) {
+            for (int t = threadIdx.x; t < 8 * mn; t += 1024) {
                 const int k = t & 7, m = m0 + (t >> 3);
                 if (np + k < g.lp) g.Ws[g.ldt ? (np + k) * g.ldt + m : m * g.lp + np + k] = 0.0;
                 if (nm + k < g.lm) g.Wa[g.ldt ? (nm + k) * g.ldt + m : m * g.lm + nm + k] = 0.0;
             }
         }
-        const int half = g.nv * v;
-        for (int r = blockIdx.y; r < g.nrow0; r += gridDim.y)
-            for (int c = threadIdx.x; c < half; c += 256) g.Y0[r * g.ldy + half + c] = 0.0;
         return;
     }
     int tc = 0, p = blockIdx.x;
@@ -65,24 +68,24 @@ __global__ __launch_bounds__(256) void sigma_prep_kernel(SigmaPrep g) {
     {
         const int c = c0 + ty, d = d0 + tx, c2 = c0 + tx, d2 = d0 + ty;
         const bool in = c < v && d < v, im = c2 < v && d2 < v;
-        double ra[PT], rb[PT];  // every load issued before the first is waited for
+        double ra[4], rb[4];  // every load issued before the first is waited for
 #pragma unroll
-        for (int m = 0; m < PT; ++m) {
-            const int mm = min(m0 + m, M - 1), n = mm / o, j = mm - n * o;
+        for (int m = 0; m < 4; ++m) {
+            const int mm = min(m0 + 4 * tz + m, M - 1), n = mm / o, j = mm - n * o;
             const double* zb = g.z + n * g.ldz + (long long)j * vv;
             ra[m] = in ? zb[c * v + d] : 0.0;    // z[c][d]
             rb[m] = im ? zb[d2 * v + c2] : 0.0;  // z[d][c]
         }
 #pragma unroll
-        for (int m = 0; m < PT; ++m) {
-            A[m * PM + ty * PR + tx] = ra[m];
-            B[m * PM + ty * PR + tx] = rb[m];
+        for (int m = 0; m < 4; ++m) {
+            A[(4 * tz + m) * PM + ty * PR + tx] = ra[m];
+            B[(4 * tz + m) * PM + ty * PR + tx] = rb[m];
         }
     }
     __syncthreads();
     if (g.Ws) {
         if (g.ldt) {
-            for (int e = ty; e < PT * PT; e += 16) {  // lanes along m
+            for (int e = threadIdx.x >> 4; e < PT * PT; e += 64) {  // lanes along m
                 const int ci = e >> 4, di = e & 15, c = c0 + ci, d = d0 + di;
                 if (c > d || d >= v || tx >= mn) continue;
                 const double x = A[tx * PM + ci * PR + di], y = B[tx * PM + di * PR + ci];
@@ -97,7 +100,7 @@ __global__ __launch_bounds__(256) void sigma_prep_kernel(SigmaPrep g) {
         } else {
             const int c = c0 + ty, d = d0 + tx;  // lanes along d
             if (c <= d && d < v)
-                for (int m = 0; m < mn; ++m) {
+                for (int m = tz; m < mn; m += 4) {
                     const double x = A[m * PM + ty * PR + tx], y = B[m * PM + tx * PR + ty];
                     if (c == d) {
                         g.Ws[(m0 + m) * g.lp + pidx(c, c, v)] = x;
@@ -109,8 +112,7 @@ __global__ __launch_bounds__(256) void sigma_prep_kernel(SigmaPrep g) {
         }
     }
     const double is3 = 0.57735026918962576451;  // 1/sqrt(3)
-    const int half = g.nv * v;
-    for (int m = 0; m < mn; ++m) {
+    for (int m = tz; m < mn; m += 4) {
         const int n = (m0 + m) / o, j = (m0 + m) - n * o;
         {  // rows (j, d = d0 + ty), columns (n, c = c0 + tx)
             const int c = c0 + tx, d = d0 + ty;
@@ -219,7 +221,7 @@ void k_sigma_prep(const double* z, long long ldz, int nv, int o, int v, double* 
     g.Ws = Ws; g.Wa = Wa; g.ldt = ldt; g.lp = sa_lp(v); g.lm = sa_lm(v);
     g.Y1 = Y1; g.ldy1 = ldy1; g.Y23 = Y23; g.ldy = ldy; g.Y0 = Y0; g.nrow0 = nrow0;
     const int nt = (v + PT - 1) / PT;
-    hipLaunchKernelGGL(sigma_prep_kernel, dim3((unsigned)(nt * (nt + 1) / 2 + 1), (unsigned)((nv * o + PT - 1) / PT)), dim3(256),
+    hipLaunchKernelGGL(sigma_prep_kernel, dim3((unsigned)(nt * (nt + 1) / 2 + 1), (unsigned)((nv * o + PT - 1) / PT)), dim3(1024),
                        0, s, g);
     LAUNCHCHK();
 }
