@@ -134,6 +134,8 @@ bool ladder_dual_tuned(const LadderTProb* p, int np, int M, int tm, int mtiles, 
 // row tiling and K per chunk of the two pair blocks' launch: modelled (km_shape), or ADC3_LADDER_CHUNKS chunks; false if
 // no chunking fits both the 31-bit tile offsets and the partial sums' room
 bool ladder_t_shape(int M, long long lp, long long lm, long long ldz, long long partial, int& tm, int& mt, int& kc);
+// rows of each of mtiles row tiles of the k-major kernel over M rows: 16-row blocks and up to two 4-row strips
+int ladder_t_rows(long long M, long long mtiles);
 // the modelled row tiling and K per chunk (tensor.hip): N columns in all, partial sums of at most partial elements
 void km_shape(long long M, long long N, long long K, long long partial, int kcmax, int& tm, int& mt, int& kc);
 // FP32 operands (FP32 accumulation, FP64 partial sums / output), Z k-major, ldz and ldg multiples of 4

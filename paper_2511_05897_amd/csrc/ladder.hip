@@ -217,11 +217,16 @@ __device__ inline void block_tile(int nchunk, int ntn, int& chunk, int& nt) {
 
 // One launch may hold two products of the same row count and chunk count (grid z = 2: the ladder's two pair blocks),
 // so that they share the chip's last round.
-template <int TM, int TAG>
+//
+// A tile has 16 TM + 4 EX rows.  The 4-row strips take v_mfma_f64_4x4x4 (four 4x4x4 blocks, the rate of the 16x16x4 form:
+// 16 cycles against 64), its four blocks on four times four columns: its B operand is the 16x16x4 form's, its A operand the
+// strip's rows in lanes l % 4, k = l / 16 in both.  A sigma's row counts are nv o, seldom a multiple of 16: 100 rows cost
+// 400 cycles a step, not 448 (o=20 v=200, 5 vectors: both pair blocks 2.93 -> 2.58 ms, 62 TFLOP/s).
+template <int TM, int EX, int TAG>
 __global__ __launch_bounds__(LNT, 2) void ladder_f64t_kernel(LadderArgs g0, LadderArgs g1) {
     const LadderArgs& g = blockIdx.z ? g1 : g0;
     if ((int)blockIdx.x >= g.nchunk * g.ntn) return;
-    constexpr int BM = 16 * TM, RA = BM + 2, RB = LBN + 2;  // LDS row strides (doubles)
+    constexpr int BM = 16 * TM + 4 * EX, RA = BM + 2, RB = LBN + 2;  // LDS row strides (doubles)
     __shared__ __attribute__((aligned(16))) double As0[LBK][RA], As1[LBK][RA];
     __shared__ __attribute__((aligned(16))) double Bs0[LBK][RB], Bs1[LBK][RB];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -254,6 +259,11 @@ __global__ __launch_bounds__(LNT, 2) void ladder_f64t_kernel(LadderArgs g0, Ladd
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < LTN; ++j) acc[i][j] = d4v{0.0, 0.0, 0.0, 0.0};
+    double ax[EX > 0 ? EX : 1][LTN];
+#pragma unroll
+    for (int e = 0; e < EX; ++e)
+#pragma unroll
+        for (int j = 0; j < LTN; ++j) ax[e][j] = 0.0;
     const int cb = wave * (16 * LTN);
     // Rows and columns are dealt to the MFMA blocks in interleaved pairs, so that one 16-byte LDS read
     // fetches the fragments of two blocks: row block 2h+e holds rows 32h + 2t + e, column block j holds
@@ -275,6 +285,12 @@ __global__ __launch_bounds__(LNT, 2) void ladder_f64t_kernel(LadderArgs g0, Ladd
                 const double af = At[kk + lk][16 * (TM - 1) + lr];
                 acc[TM - 1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(af, bq.x, acc[TM - 1][0], 0, 0, 0);
                 acc[TM - 1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(af, bq.y, acc[TM - 1][1], 0, 0, 0);
+            }
+#pragma unroll
+            for (int e = 0; e < EX; ++e) {
+                const double af = At[kk + lk][16 * TM + 4 * e + (lr & 3)];
+                ax[e][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(af, bq.x, ax[e][0], 0, 0, 0);
+                ax[e][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(af, bq.y, ax[e][1], 0, 0, 0);
             }
         }
     };
@@ -298,6 +314,16 @@ __global__ __launch_bounds__(LNT, 2) void ladder_f64t_kernel(LadderArgs g0, Ladd
         sync();
     }
     if (s < nslab) compute(As0, Bs0);
+    auto put = [&](long long row, long long col, double x) {
+        if (row >= g.M || col >= g.N) return;
+        if (g.nchunk > 1) {
+            g.P[((long long)chunk * g.M + row) * g.N + col] = x;
+        } else {
+            double* c = g.C + row * g.ldc + col;
+            const double v = g.alpha * x;
+            *c = (g.beta == 0.0) ? v : v + g.beta * (*c);
+        }
+    };
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -305,18 +331,13 @@ __global__ __launch_bounds__(LNT, 2) void ladder_f64t_kernel(LadderArgs g0, Ladd
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int t = lk + 4 * r;  // the block's output row
-                const long long row = m0 + ((TM & 1) && i == TM - 1 ? 16 * i + t : 32 * (i >> 1) + 2 * t + (i & 1));
-                const long long col = n0 + cb + 2 * lr + j;
-                if (row < g.M && col < g.N) {
-                    if (g.nchunk > 1) {
-                        g.P[((long long)chunk * g.M + row) * g.N + col] = acc[i][j][r];
-                    } else {
-                        double* c = g.C + row * g.ldc + col;
-                        const double v = g.alpha * acc[i][j][r];
-                        *c = (g.beta == 0.0) ? v : v + g.beta * (*c);
-                    }
-                }
+                put(m0 + ((TM & 1) && i == TM - 1 ? 16 * i + t : 32 * (i >> 1) + 2 * t + (i & 1)), n0 + cb + 2 * lr + j,
+                    acc[i][j][r]);
             }
+#pragma unroll
+    for (int e = 0; e < EX; ++e)
+#pragma unroll
+        for (int j = 0; j < LTN; ++j) put(m0 + 16 * TM + 4 * e + lk, n0 + cb + 2 * lr + j, ax[e][j]);
 }
 
 // ---------------------------------------------------------------------------
@@ -683,23 +704,42 @@ void launch(const LadderArgs& a, int tm, int mtiles, int tag, hipStream_t s) {
     LAUNCHCHK();
 }
 
-template <int TM, int TAG>
-void launch_t_tm(const LadderArgs& a, const LadderArgs* b, int mtiles, hipStream_t s) {
-    const int gx = std::max(a.nchunk * a.ntn, b ? b->nchunk * b->ntn : 0);
-    hipLaunchKernelGGL((ladder_f64t_kernel<TM, TAG>), dim3(gx, mtiles, b ? 2 : 1), dim3(LNT), 0, s, a, b ? *b : a);
+}  // namespace
+
+int ladder_t_rows(long long M, long long mtiles) {
+    const int r = (int)std::max<long long>(16, ((M + mtiles - 1) / mtiles + 3) / 4 * 4);
+    return r % 16 == 12 ? r + 4 : r;
 }
 
+namespace {
+template <int TM, int EX, int TAG>
+void launch_t_tm(const LadderArgs& a, const LadderArgs* b, int mtiles, hipStream_t s) {
+    const int gx = std::max(a.nchunk * a.ntn, b ? b->nchunk * b->ntn : 0);
+    hipLaunchKernelGGL((ladder_f64t_kernel<TM, EX, TAG>), dim3(gx, mtiles, b ? 2 : 1), dim3(LNT), 0, s, a, b ? *b : a);
+}
+
+template <int TM, int TAG>
+void launch_t_ex(const LadderArgs& a, const LadderArgs* b, int ex, int mtiles, hipStream_t s) {
+    if constexpr (TM < 8) {
+        if (ex == 1) return launch_t_tm<TM, 1, TAG>(a, b, mtiles, s);
+        if (ex == 2) return launch_t_tm<TM, 2, TAG>(a, b, mtiles, s);
+    }
+    launch_t_tm<TM, 0, TAG>(a, b, mtiles, s);
+}
+
+// mtiles row tiles of the least height that covers M (at most 16 tm rows)
 template <int TAG>
 void launch_t_tag(const LadderArgs& a, const LadderArgs* b, int tm, int mtiles, hipStream_t s) {
-    switch (tm) {
-        case 1: launch_t_tm<1, TAG>(a, b, mtiles, s); break;
-        case 2: launch_t_tm<2, TAG>(a, b, mtiles, s); break;
-        case 3: launch_t_tm<3, TAG>(a, b, mtiles, s); break;
-        case 4: launch_t_tm<4, TAG>(a, b, mtiles, s); break;
-        case 5: launch_t_tm<5, TAG>(a, b, mtiles, s); break;
-        case 6: launch_t_tm<6, TAG>(a, b, mtiles, s); break;
-        case 7: launch_t_tm<7, TAG>(a, b, mtiles, s); break;
-        default: launch_t_tm<8, TAG>(a, b, mtiles, s); break;
+    const int rows = std::min(16 * tm, ladder_t_rows(a.M, mtiles)), ex = rows % 16 / 4;
+    switch (rows / 16) {
+        case 1: launch_t_ex<1, TAG>(a, b, ex, mtiles, s); break;
+        case 2: launch_t_ex<2, TAG>(a, b, ex, mtiles, s); break;
+        case 3: launch_t_ex<3, TAG>(a, b, ex, mtiles, s); break;
+        case 4: launch_t_ex<4, TAG>(a, b, ex, mtiles, s); break;
+        case 5: launch_t_ex<5, TAG>(a, b, ex, mtiles, s); break;
+        case 6: launch_t_ex<6, TAG>(a, b, ex, mtiles, s); break;
+        case 7: launch_t_ex<7, TAG>(a, b, ex, mtiles, s); break;
+        default: launch_t_ex<8, TAG>(a, b, ex, mtiles, s); break;
     }
 }
 }  // namespace

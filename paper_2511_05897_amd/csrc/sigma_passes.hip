@@ -28,7 +28,7 @@ __device__ inline long long qidx(int a, int b, int v) {  // a < b
 // (along d and c of z, along c and d of the operands' columns, along m of the k-major packed rows).  16 waves a workgroup:
 // a small sigma has few tile pairs and waits for each (one vector of o=16 v=120, 37 workgroups: 26 us with four waves,
 // 9.3
-// with 16; five of o=20 v=200: 42 and @@P2@@).
+// with 16; five of o=20 v=200: 42 and 35).
 constexpr int PT = 16, PR = 17, PM = PT * PR + 1;  // tile, LDS row stride, stride between rows m
 
 struct SigmaPrep {

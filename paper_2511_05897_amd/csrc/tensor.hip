@@ -58,21 +58,22 @@ void permute_any(double* out, const double* in, const std::string& from, const i
 }  // namespace
 
 // The tile and K split of a k-major product: the least modelled time over row tiles of 16 tm rows and K chunks.
-// A workgroup's slab of 16 k keeps each of a CU's four matrix cores busy for 512 tm cycles; a CU with one workgroup
+// A workgroup's slab of 16 k keeps each of a CU's four matrix cores busy for 512 cycles per 16 rows; a CU with one workgroup
 // also waits for the slab's loads (about 700 cycles), with two that mostly overlaps (400); B streams from HBM once per
-// row tile; a split adds a pass over the partial sums and a launch.  The sigma ladder at v = 200, 100 rows: 2.84 ms
-// modelled, 2.95 measured; o=13 v=91, 65 rows: 97 and 107 us.
+// row tile; a split adds a pass over the partial sums and a launch.  (The sigma ladder at o=13 v=91, 65 rows, on this
+// choice: 101 us for both pair blocks; measured choices for one block at a time, used for both: 162.)
 void km_shape(long long M, long long N, long long K, long long partial, int kcmax, int& tm, int& mt, int& kc) {
     const long long ntn = (N + 127) / 128, nb = (M + 15) / 16;
     double best = 1e300;
     for (int t = (int)std::min<long long>(8, nb); t >= 1; --t) {
         const long long m = (nb + t - 1) / t;
         if (m > 65535) continue;
+        const double blocks = ladder_t_rows(M, m) / 16.0;
         for (int c = 1; c <= 32; ++c) {
             const long long k = ((K + c - 1) / c + 15) / 16 * 16, n = (K + k - 1) / k;
             if (k > kcmax || (n > 1 && n * M * N > partial) || (c > 1 && k < 64)) continue;
             const double w = (double)m * ntn * n, slabs = (double)k / 16;
-            double cost = std::ceil(w / 256.0) * slabs * (512.0 * t + (w <= 256 ? 700.0 : 400.0)) + 3000.0;
+            double cost = std::ceil(w / 256.0) * slabs * (512.0 * blocks + (w <= 256 ? 700.0 : 400.0)) + 3000.0;
             cost = std::max(cost, 8.0 * (double)m * N * K / 5.2e12 * 2.2e9);  // B streamed once per row tile
             if (n > 1) cost += 7000.0 + 2.2e9 * (8.0 * (n + 1) * M * N) / 3.5e12;
             if (cost < best) { best = cost; tm = t; mt = (int)m; kc = (int)k; }
