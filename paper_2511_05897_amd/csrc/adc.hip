@@ -638,8 +638,12 @@ static void sigma_pass(Ctx* c, Arena& ws, const double* rr, double* ss, int nv, 
             if (!g_dry && !rows3 && !ladder_dual_tuned(pr, lm > 0 ? 2 : 1, M, tm, mt, kc, CW, pbuf, pe, s))
                 dual = false;
         }
+        // up to 20 rows of streamed blocks: half of each symmetric G is read (whole sigma,
+        // row-major streaming kernel and this one: 5 rows of v=91 110 -> 88 us, 20 rows 187 -> 162; v=200, 10 rows 1434 ->
+        // 1000, 20 rows 1816 -> 1404; more rows would not fit the registers, and from 33 on the matrix cores bound it)
+        const bool sym = stored && prec == 0 && !dual && lp >= LADDER_STREAM_MIN && ladder_sym_fits(M, lp, lm, pe);
         const long long nmin = km64 ? ladder_t_min_chunks((int)lp, ldt8, lp) : 0;
-        const bool kmajor = prec == 0 ? dual || (rows3 && nmin > 0 && nmin * M * lp <= pe) : stored && rows3;
+        const bool kmajor = prec == 0 ? dual || sym || (rows3 && nmin > 0 && nmin * M * lp <= pe) : stored && rows3;
         const long long ldt = !kmajor ? 0 : prec == 1 ? ldt4 : ldt8;
         const long long woff = kmajor ? ldt * lp : (long long)M * lp;
         double* Wm = stored ? W + woff : nullptr;
@@ -677,6 +681,14 @@ static void sigma_pass(Ctx* c, Arena& ws, const double* rr, double* ss, int nv, 
             nl = ladder_t_partials(pr, lm > 0 ? 2 : 1, M, tm, mt, kc, 0x7fffffff, 0, 0, s);
             Cs = pr[0].P;
             Cm = pr[1].P;
+        } else if (sym && !g_dry && ladder_t_supported(M, (int)lp, (int)lp, W, ldt, c->G, lp) &&
+                   ladder_t_supported(M, (int)lm, (int)lm, Wm, ldt, c->Gm, lm)) {
+            const double fl = 2.0 * M * ((double)lp * lp + (double)lm * lm);
+            const double by = 4.0 * ((double)lp * lp + (double)lm * lm) + 16.0 * M * (double)(lp + lm);
+            ProfScope p(PROF_LADDER, s, fl, by, 1e3 * std::max(fl / PEAK_FP64_MFMA, by / PEAK_HBM));
+            ladder_sym(M, W, Wm, ldt, c->G, (int)lp, c->Gm, (int)lm, CW, CW + (long long)M * lp, pbuf, s);
+            Cs = CW;
+            Cm = CW + (long long)M * lp;
         } else {
             // one launch per block: the row-major FP64 kernel, or the reduced precisions
             float* Wt32 = prec == 1 ? (float*)take(ws, ((M + 3) / 4 * 4 * (lp + lm) + 1) / 2) : nullptr;

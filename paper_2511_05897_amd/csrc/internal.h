@@ -127,6 +127,11 @@ struct LadderTProb {
 };
 int ladder_t_partials(const LadderTProb* p, int np, int M, int tm, int mtiles, int kc, int row_skip, int k_skip, int tag,
                       hipStream_t s);
+// both pair blocks' products for M <= 20 rows from half of each symmetric G (ladder_sym.hip): Z k-major (rows of ldz), G and
+// C with rows of np, nm; partial sums in partial.  Whether the sizes are supported and `partial` doubles suffice:
+bool ladder_sym_fits(int M, long long np, long long nm, long long partial);
+void ladder_sym(int M, const double* Zp, const double* Zm, long long ldz, const double* Gp, int np, const double* Gm, int nm,
+                double* Cp, double* Cm, double* partial, hipStream_t s);
 // whether that one launch beats the row-major kernel block by block: measured once per shape (the buffers' values do not
 // matter) and kept with the tuner's other choices
 bool ladder_dual_tuned(const LadderTProb* p, int np, int M, int tm, int mtiles, int kc, double* C, double* partial,
