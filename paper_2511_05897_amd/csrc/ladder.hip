@@ -57,7 +57,7 @@ struct LadderArgs {
     int row_skip = 0x7fffffff, k_skip = 0;
 };
 
-// TAG 1 marks the tuner's trial launches, TAG 2 other large GEMMs on this tile (separate symbols
+// TAG 1 marks the tuner's trial launches, TAG 2 and 3 other large GEMMs on this tile (separate symbols
 // for profilers).
 template <int TM, int TAG>
 __global__ __launch_bounds__(LNT, 2) void ladder_f64_kernel(LadderArgs g) {
@@ -215,6 +215,19 @@ __device__ inline void block_tile(int nchunk, int ntn, int& chunk, int& nt) {
     }
 }
 
+// The tile of one workgroup in a product without a K split and of more than two rounds of the chip (TAG 3; up to there the
+// order did not matter): tiles are dealt to the XCDs in contiguous ranges of an order that runs down eight row strips before
+// the next column.  The 64 workgroups that one XCD runs together then form an 8 x 8 patch whose rows and columns its L2
+// serves, and G is fetched once per eight row strips (once per strip with the strips outermost: 4000 x 40000 x 4000 in
+// 20.1 ms, here 19.0, 67 TFLOP/s).
+__device__ inline void patch_tile(int ntn, int& nt, int& mt) {
+    const unsigned mtiles = gridDim.y, T = gridDim.x * mtiles, L = blockIdx.y * gridDim.x + blockIdx.x, x = L & 7;
+    const unsigned seq = x * (T >> 3) + min(x, T & 7u) + (L >> 3);
+    const unsigned gi = seq / (8u * ntn), rem = seq - gi * 8u * ntn, gm = min(8u, mtiles - 8 * gi);
+    nt = rem / gm;
+    mt = 8 * gi + rem % gm;
+}
+
 // One launch may hold two products of the same row count and chunk count (grid z = 2: the ladder's two pair blocks),
 // so that they share the chip's last round.
 //
@@ -231,9 +244,10 @@ __global__ __launch_bounds__(LNT, 2) void ladder_f64t_kernel(LadderArgs g0, Ladd
     __shared__ __attribute__((aligned(16))) double Bs0[LBK][RB], Bs1[LBK][RB];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lr = lane & 15, lk = lane >> 4;
-    int chunk, nt;
-    block_tile(g.nchunk, g.ntn, chunk, nt);
-    const long long m0 = (long long)blockIdx.y * BM, n0 = (long long)nt * LBN;
+    int chunk = 0, nt, mt = blockIdx.y;
+    if constexpr (TAG == 3) patch_tile(g.ntn, nt, mt);
+    else block_tile(g.nchunk, g.ntn, chunk, nt);
+    const long long m0 = (long long)mt * BM, n0 = (long long)nt * LBN;
     const int ke = min(g.K, (chunk + 1) * g.Kc);
     const int kb = min(ke, m0 >= g.row_skip ? max(chunk * g.Kc, g.k_skip) : chunk * g.Kc);
     const __amdgpu_buffer_rsrc_t ra = chunk_rsrc(g.Z + (long long)kb * g.ldz + m0, (long long)(ke - kb) * g.ldz * 8 - m0 * 8);
@@ -904,7 +918,8 @@ void ladder_gemm_t_shape(int M, int N, int K, double alpha, const double* Zt, lo
     a.nchunk = (K + kc - 1) / kc;
     a.ntn = (N + LBN - 1) / LBN;
     a.alpha = alpha; a.beta = beta;
-    launch_t_tag<2>(a, nullptr, tm, mtiles, s);
+    if (a.nchunk == 1 && mtiles > 1 && (long long)a.ntn * mtiles > 1024) launch_t_tag<3>(a, nullptr, tm, mtiles, s);
+    else launch_t_tag<2>(a, nullptr, tm, mtiles, s);
     LAUNCHCHK();
     if (a.nchunk > 1) splitk_reduce(partial, a.nchunk, M, N, alpha, beta, C, ldc, 1, s);
 }
