@@ -83,7 +83,7 @@ struct PinnedStage {
 constexpr size_t PIN_BYTES = 1 << 20;
 static double* host_stage() {
     thread_local PinnedStage pin;
-    if (!pin.p) HIPCHK(hipHostMalloc(&pin.p, PIN_BYTES, hipHostMallocDefault));
+    if (!pin.p) HIPCHK(hipHostMalloc(&pin.p, PIN_BYTES, hipHostMallocPortable | hipHostMallocMapped));
     return (double*)pin.p;
 }
 
