@@ -79,13 +79,12 @@ def parse():
 # for a copy of known size.  Keyed by a hash of the kernel's source and of the pair-block packing
 # that sets its launch shapes: a change to either reports null until it is measured again.
 LADDER_TRAFFIC = {
-    "25bbecc6313e593a": {
-        "bytes_per_launch": 3.436e9, "read_bytes": 3.307e9, "written_bytes": 0.129e9,
+    "540b91534ad136e7": {
+        "bytes_per_launch": 7.185e9, "read_bytes": 7.056e9, "written_bytes": 0.129e9,
         "fetch_scale": 2.0, "write_scale": 1.0,
-        "measured_on": "sigma ladder o=20 v=200 X=128, 5 vectors (M=100, ladder_f64t_kernel), 8 K-chunks (fixed "
-                       "with ADC3_LADDER_CHUNKS=8; the tuner takes 8 or 16, and 16 adds 0.13 GB of partial sums to a "
-                       "launch); mean of the pair-symmetric (3.478 GB) and pair-antisymmetric (3.394 GB) block launches",
-        "profile": "profiles/ladder_f64t_o20v200x128_sigma_counters.md"},
+        "measured_on": "sigma ladder o=20 v=200 X=128, 5 vectors (M=100, ladder_f64t_kernel), both pair blocks in one launch, "
+                       "2 K-chunks",
+        "profile": "profiles/sigma_o20v200x128_kernels.md"},
 }
 
 
@@ -864,7 +863,8 @@ def main():
         "sigma_builds_per_step": nsig / a.steps,
         "sigma_builds_adc3_per_step": nsig3 / a.steps,
         "sigma_adc3_per_s_whole_solve": nsig3 / dt,
-        "roofline": {"kernel": "sigma ladder (ladder_f64t_kernel; ladder_f64_kernel for row tiles of <= 32 rows)",
+        "roofline": {"kernel": "sigma ladder (ladder_f64t_kernel, both pair blocks in one launch; ladder_sym_kernel up to 20 "
+                               "rows, ladder_f64_kernel for 21 to 32)",
                      "bound": "mfma",
                      "achieved": rf["achieved"], "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
                      "frac": rf["achieved"] / PEAK_FP64_TFLOPS,
