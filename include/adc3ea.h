@@ -283,7 +283,8 @@ int adc3_ladder_apply_static(const double* Bvv_dev, const double* Z_dev, double*
  * "Frozen Natural Orbitals", eq 9 and the recanonicalisation of eqs 12-13; Sec. "Natural
  * Auxiliary Functions", eq 28): FP64 cyclic Jacobi (n > 96: over blocks of 16 rows, each round's
  * block-pair sub-matrices swept in LDS and their orthogonal factors applied to A and V, the
- * eigenvalues then taken as Rayleigh quotients with the input matrix).
+ * eigenvalues then taken as Rayleigh quotients with the input matrix and the vectors corrected
+ * to first order against it).
  * A_dev[n][n] device, row-major, read only
  * (its symmetric part (A + A^T)/2 is diagonalised); w_dev[n] receives the eigenvalues in
  * ascending order, V_dev[n][n] the eigenvectors as columns (V[i][k] = component i of vector k),

@@ -529,8 +529,8 @@ __global__ void bj_start_kernel(const double* A, double* A0, double* Vt, int n) 
 
 // w[b][i] = v_i^T A0 v_i / v_i^T v_i for 16 vectors (rows of Vt) per workgroup: the rotated diagonal carries the
 // rounding of every round (2e-15 relative), the Rayleigh quotient only that of its own products (6e-16); 16
-// waves deal out the 16-column tiles of Vt A0.
-__global__ __launch_bounds__(1024) void bj_rayleigh_kernel(const double* A0, const double* Vt, int n, double* w) {
+// waves deal out the 16-column tiles of Vt A0, which goes to W.
+__global__ __launch_bounds__(1024) void bj_rayleigh_kernel(const double* A0, const double* Vt, int n, double* w, double* W) {
     const long long o = (long long)blockIdx.y * n * n;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lk = lane >> 4;
     const int i0 = blockIdx.x * 16, nt = (n + 15) / 16;
@@ -549,7 +549,9 @@ __global__ __launch_bounds__(1024) void bj_rayleigh_kernel(const double* A0, con
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int i = i0 + lk + 4 * e;
-            const double v = (i < n && col < n) ? Vt[o + (long long)i * n + col] : 0.0;
+            const bool in = i < n && col < n;
+            const double v = in ? Vt[o + (long long)i * n + col] : 0.0;
+            if (in) W[o + (long long)i * n + col] = acc[e];
             num[e] += acc[e] * v;
             den[e] += v * v;
         }
@@ -569,6 +571,80 @@ __global__ __launch_bounds__(1024) void bj_rayleigh_kernel(const double* A0, con
         for (int k = 0; k < 16; ++k) { a += sn[k][threadIdx.x]; b += sd[k][threadIdx.x]; }
         w[(long long)blockIdx.y * n + i0 + threadIdx.x] = a / b;
     }
+}
+
+// The rotated vectors carry the rounding of every round too: V^T A0 V is diagonal only to 28 eps of the norm at
+// n = 600 (14 at n = 200), which an eigenvector pair shows divided by its gap.  One first-order correction from the
+// input matrix takes that out:  x_j += sum_i E_ij x_i  with, for r = I - V^T V and the residuals q_j = A0 x_j - w_j x_j,
+//   E_ij = x_i . q_j / (w_j - w_i),   E_ji = r_ij - E_ij,   E_ii = r_ii / 2,
+// and E_ij = E_ji = r_ij / 2 (orthogonality alone) for a pair whose rotation would exceed 2^-26, where the neglected square
+// is no longer below the rounding: clusters, whose vectors are any basis of their space.  Both elements of a pair come
+// from one workgroup and one decision, so the correction is antisymmetric up to r.
+// grid (nt (nt + 1) / 2, batch), 256 threads: the 16 x 16 tile pair (i tile <= j tile), K dealt to the waves; E[i][j].
+__global__ __launch_bounds__(256) void bj_correct_kernel(const double* Vt, const double* W, const double* w, int n, double* E) {
+    const long long o = (long long)blockIdx.y * n * n;
+    const double* wb = w + (long long)blockIdx.y * n;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lk = lane >> 4;
+    const int nt = (n + 15) / 16;
+    int ti = 0, p = blockIdx.x;
+    while (p >= nt - ti) { p -= nt - ti; ++ti; }
+    const int tj = ti + p, i = ti * 16 + lr, j = tj * 16 + lr;
+    const bool ii = i < n, ij = j < n;
+    const double* vi = Vt + o + (long long)(ii ? i : 0) * n;
+    const double* vj = Vt + o + (long long)(ij ? j : 0) * n;
+    const double* Wj = W + o + (long long)(ij ? j : 0) * n;
+    const double wj = ij ? wb[j] : 0.0;
+    d4e g = {0.0, 0.0, 0.0, 0.0}, q = g;
+    for (int k0 = 16 * wave; k0 < n; k0 += 64)  // step s: k = k0 + 4 lk + s on both sides
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int k = k0 + 4 * lk + s;
+            const double a = (ii && k < n) ? vi[k] : 0.0, b = (ij && k < n) ? vj[k] : 0.0;
+            const double c = (ij && k < n) ? fma(-wj, b, Wj[k]) : 0.0;
+            g = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, g, 0, 0, 0);
+            q = __builtin_amdgcn_mfma_f64_16x16x4f64(a, c, q, 0, 0, 0);
+        }
+    __shared__ double sg[4][256], sq[4][256];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        sg[wave][(lk + 4 * e) * 16 + lr] = g[e];
+        sq[wave][(lk + 4 * e) * 16 + lr] = q[e];
+    }
+    __syncthreads();
+    const int t = threadIdx.x, x = ti * 16 + (t >> 4), y = tj * 16 + (t & 15);
+    if (x > y || y >= n) return;
+    const double gs = ((sg[0][t] + sg[1][t]) + sg[2][t]) + sg[3][t], qs = ((sq[0][t] + sq[1][t]) + sq[2][t]) + sq[3][t];
+    const double gap = wb[y] - wb[x], r = (x == y ? 1.0 : 0.0) - gs;
+    const bool rot = x != y && fabs(qs) <= 0x1p-26 * fabs(gap);
+    const double exy = rot && gap != 0.0 ? qs / gap : 0.5 * r;
+    E[o + (long long)x * n + y] = exy;
+    if (x != y) E[o + (long long)y * n + x] = r - exy;
+}
+
+// V[k][j] = Vt[j][k] + sum_i E[i][j] Vt[i][k]: grid (nt, nt, batch), 256 threads, a 16 x 16 tile (j, k), i dealt to the
+// waves; written transposed (vectors as columns) through LDS.
+__global__ __launch_bounds__(256) void bj_update_kernel(const double* Vt, const double* E, int n, double* V) {
+    const long long o = (long long)blockIdx.z * n * n;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lk = lane >> 4;
+    const int j0 = blockIdx.x * 16, k0 = blockIdx.y * 16, j = j0 + lr, k = k0 + lr;
+    d4e d = {0.0, 0.0, 0.0, 0.0};
+    for (int i0 = 16 * wave; i0 < n; i0 += 64)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int i = i0 + 4 * s + lk;
+            const double a = (i < n && j < n) ? E[o + (long long)i * n + j] : 0.0;
+            const double b = (i < n && k < n) ? Vt[o + (long long)i * n + k] : 0.0;
+            d = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, d, 0, 0, 0);
+        }
+    __shared__ double sd[4][16][17];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sd[wave][lk + 4 * e][lr] = d[e];
+    __shared__ double vt[16][17];
+    const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
+    vt[r][c] = (j0 + r < n && k0 + c < n) ? Vt[o + (long long)(j0 + r) * n + k0 + c] : 0.0;
+    __syncthreads();
+    if (k0 + r < n && j0 + c < n)
+        V[o + (long long)(k0 + r) * n + j0 + c] = vt[c][r] + (((sd[0][c][r] + sd[1][c][r]) + sd[2][c][r]) + sd[3][c][r]);
 }
 }  // namespace
 
@@ -666,9 +742,12 @@ void eig_block(double* A, int n, int nb, double* w, double* V, double* scratch, 
         }
         LAUNCHCHK();
     }
-    hipLaunchKernelGGL(bj_rayleigh_kernel, dim3((n + 15) / 16, nb), dim3(1024), 0, s, A0, Vt, n, w);
+    // A is free from here on (it takes Vt A0), and A0 after the quotients (it takes the correction)
+    const int nt = (n + 15) / 16;
+    hipLaunchKernelGGL(bj_rayleigh_kernel, dim3(nt, nb), dim3(1024), 0, s, A0, Vt, n, w, A);
+    hipLaunchKernelGGL(bj_correct_kernel, dim3(nt * (nt + 1) / 2, nb), dim3(256), 0, s, Vt, A, w, n, A0);
+    hipLaunchKernelGGL(bj_update_kernel, dim3(nt, nt, nb), dim3(256), 0, s, Vt, A0, n, V);
     LAUNCHCHK();
-    for (int b = 0; b < nb; ++b) k_transpose(Vt + b * nn, n, n, n, V + b * nn, n, s);
 }
 }  // namespace
 
