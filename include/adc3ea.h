@@ -352,6 +352,12 @@ void adc3_debug_inject_nan(int iteration);
  * 0 restores it.  Results are the same up to summation order. */
 void adc3_debug_ladder_offset_limit(long long bytes);
 
+/* Test hook of the workspace plan (host only): bytes that a truncating solve uses when its bases keep nvir_kept virtuals
+ * (1..nvir) and naux_kept auxiliary functions (0: all), with the NAF truncation on or off.  For all of them
+ * adc3_ea_solve_workspace_bytes must be as much; 0 for invalid arguments. */
+size_t adc3_debug_kept_workspace_bytes(int nocc, int nvir, int naux, int nroots, const adc3_opts* opts,
+                                       int nvir_kept, int naux_kept, int naf);
+
 /* Test hook: dense M (N <= 20000) into M_dev[N][ldm] device. */
 int adc3_ea_dense_matrix(adc3_ctx* ctx, double* M_dev, int ldm, hipStream_t stream);
 

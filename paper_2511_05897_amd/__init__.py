@@ -29,7 +29,7 @@ EXPORTS = ["adc3_default_opts", "adc3_last_error", "adc3_ea_solve_workspace_byte
            "adc3_ladder_workspace_bytes", "adc3_ladder_apply", "adc3_eigh_workspace_bytes", "adc3_eigh",
            "adc3_eigh_batched_workspace_bytes", "adc3_eigh_batched", "adc3_ladder_apply_static",
            "adc3_ea_davidson_guess", "adc3_ea_setup_sm", "adc3_debug_inject_nan", "adc3_ea_spectral_amplitudes",
-           "adc3_debug_ladder_offset_limit"]
+           "adc3_debug_ladder_offset_limit", "adc3_debug_kept_workspace_bytes"]
 
 # size of the static device scratch of adc3_ladder_apply_static (ADC3_STATIC_SCRATCH_BYTES)
 STATIC_SCRATCH_BYTES = 256 << 20
@@ -131,6 +131,8 @@ def load():
     lib.adc3_debug_inject_nan.restype = None
     lib.adc3_debug_ladder_offset_limit.argtypes = [ctypes.c_longlong]
     lib.adc3_debug_ladder_offset_limit.restype = None
+    lib.adc3_debug_kept_workspace_bytes.argtypes = [I, I, I, I, ctypes.POINTER(adc3_opts), I, I, I]
+    lib.adc3_debug_kept_workspace_bytes.restype = S
     lib.adc3_ea_dense_matrix.argtypes = [P, P, I, P]
     lib.adc3_ea_dense_matrix.restype = I
     lib.adc3_ea_intermediate.argtypes = [P, I, P, ctypes.POINTER(LL), P]
@@ -477,6 +479,12 @@ def adc3_debug_inject_nan(iteration):
 def adc3_debug_ladder_offset_limit(nbytes):
     """Test hook: byte limit of one k-major ladder chunk's operand span (0 restores 2^31 - 1)."""
     load().adc3_debug_ladder_offset_limit(int(nbytes))
+
+
+def adc3_debug_kept_workspace_bytes(nocc, nvir, naux, nroots, nvir_kept, naux_kept=0, naf=True, opts=None):
+    """Test hook: bytes a truncating solve uses when its bases keep nvir_kept virtuals and naux_kept auxiliary functions."""
+    o = opts if opts is not None else adc3_default_opts()
+    return load().adc3_debug_kept_workspace_bytes(nocc, nvir, naux, nroots, ctypes.byref(o), nvir_kept, naux_kept, int(naf))
 
 
 def adc3_mlp_nparams():

@@ -67,6 +67,20 @@ static bool verbose() { return verbosity() >= 1; }
         }                                         \
     } while (0)
 
+// Planning of a truncating solve (plan_solve), whose kept counts are not known: the dry run takes the counts below as
+// kept (0: all), and where a size does not grow with the basis (chunks that fill a budget, K splits) counts a bound
+// over every smaller basis.
+struct KeptPlan {
+    int v = 0, X = 0;
+    bool bound = false;
+};
+static thread_local KeptPlan g_kept;
+struct KeptScope {
+    KeptPlan prev = g_kept;
+    KeptScope(int v, int X, bool bound) { g_kept = KeptPlan{v, X, bound}; }
+    ~KeptScope() { g_kept = prev; }
+};
+
 // Small read-backs go through a pinned staging buffer (one per host thread, freed when the thread
 // ends): the Davidson loop reads back a few numbers several times per iteration, and a copy into
 // pageable memory is staged by the runtime at a higher latency.
@@ -282,7 +296,9 @@ static Ctx* build_ctx(Arena& ws, const double* eo_in, const double* ev_in, const
         long long nk = std::max<long long>(1, std::min<long long>(ov / 96, (512 + tiles * o - 1) / (tiles * o)));
         const long long kc = (ov + nk - 1) / nk;
         nk = (ov + kc - 1) / kc;
-        double* part = take(ws, nk * o * vv);
+        // (a bound over smaller v: nk o is at most 512 / tiles + o with v^2 / tiles <= 64^2, and at most o^2 v / 96)
+        double* part = take(ws, g_kept.bound ? std::min(512 * 4096 + o * vv, std::max<long long>(1, ov / 96) * o * vv)
+                                             : nk * o * vv);
         Gemm g;
         g.M = v; g.N = v; g.K = (int)kc; g.Klast = (int)(ov - (nk - 1) * kc);
         g.A = L; g.sAm = ldm; g.sAk = 1; g.bA0 = kc; g.bA1 = v * ldm;
@@ -359,7 +375,13 @@ static Ctx* build_ctx(Arena& ws, const double* eo_in, const double* ev_in, const
         for (int a0 = 0; a0 < v; a0 += na) {
             const int nc = std::min(na, v - a0);
             const size_t mchunk = ws.mark();
-            const long long E = (long long)nc * v * v * o;
+            long long E = (long long)nc * v * v * o;
+            if (g_kept.bound && na < v) {
+                // chunks of smaller bases: nearly the budget, their slices of the factor at most all of it
+                E = std::max(g_chunk_elems.load(), E);
+                take(ws, X * (vv + 1));
+                take(ws, (long long)X * ov);
+            }
             double* Uc = c->Uz + (long long)a0 * o * vv;
             // the chunk's slices of Bvv [X][a][b] and Bov [X][k][a]
             const double* Bvv_a = Bvve + (long long)a0 * v;
@@ -367,11 +389,12 @@ static Ctx* build_ctx(Arena& ws, const double* eo_in, const double* ev_in, const
             gemm_km(ws, (long long)nc * v, ov, X, 1.0, Bvv_a, ldv, Bov_u, ldu, 0.0, F, ov, s);
             double *C1 = nullptr, *C2 = nullptr;
             const long long ldg = (long long)nc * v + ((long long)nc * v & 1);
+            const long long eg = g_kept.bound && na < v ? E + ov : ov * ldg;
             if (level >= 3) {
                 // sum_kl T^bc_kl (ak|il) straight into U_z [(a,i)][(b,c)]
                 gemm_km(ws, (long long)nc * o, vv, oo, x2, ooov_p + (long long)a0 * o, ov, T, vv, 0.0, Uc, vv, s);
                 // sum_kd T^bd_ki (ak|cd) and sum_kd T^cd_ik (ak|bd): both against (ka|cd) as [(k,d)][(a,c)]
-                double* G2 = take(ws, ov * ldg);
+                double* G2 = take(ws, eg);
                 {
                     const size_t m0 = ws.mark();
                     double* V1 = take(ws, E);
@@ -387,8 +410,8 @@ static Ctx* build_ctx(Arena& ws, const double* eo_in, const double* ev_in, const
                     k_ovvv_perm(G2, ldg, V1, o, nc, v, s);
                     ws.release(m0);
                 }
-                C1 = take(ws, ov * ldg);
-                C2 = take(ws, ov * ldg);
+                C1 = take(ws, eg);
+                C2 = take(ws, eg);
                 gemm_km(ws, ov, (long long)nc * v, ov, 1.0, Tx, ldm, G2, ldg, 0.0, C1, ldg, s);
                 gemm_km(ws, ov, (long long)nc * v, ov, 1.0, Tm, ldm, G2, ldg, 0.0, C2, ldg, s);
             }
@@ -428,7 +451,7 @@ static Ctx* build_ctx(Arena& ws, const double* eo_in, const double* ev_in, const
                     1, std::min<long long>({(long long)v, budget / std::max<long long>(v3, 1), 65535 / v}));
                 if (na > 1 && na < v) na -= na & 1;
                 const size_t mg = ws.mark();
-                double* Gf = take(ws, (long long)na * v3);
+                double* Gf = take(ws, g_kept.bound ? std::max(v3, std::min(budget, (long long)v * v3)) : (long long)na * v3);
                 for (int a0 = 0; a0 < v; a0 += na) {
                     const int nc = std::min(na, v - a0);
                     const long long ldf = (long long)(v - a0) * v;
@@ -1801,7 +1824,8 @@ static void natural_orbitals_all(Arena& ws, const double* Dss, const double* ev,
     d2h(hw.data(), w, (size_t)nr * v * sizeof(double), s);
     vks.assign(nr, 0);
     for (int k = 0; k < nr; ++k) {
-        if (g_dry || (keep_n <= 0 && !(thr > 0))) vks[k] = v;
+        if (g_dry) vks[k] = g_kept.v > 0 ? std::min(g_kept.v, v) : v;
+        else if (keep_n <= 0 && !(thr > 0)) vks[k] = v;
         else if (keep_n > 0) vks[k] = std::min(keep_n, v);  // a fixed share of the virtuals, largest occupations
         else
             for (int a = 0; a < v; ++a) vks[k] += hw[(size_t)k * v + a] > thr;
@@ -1899,7 +1923,8 @@ static int naf_project(const Blocks& in, double thr, const double* N, const doub
     std::vector<double> hw(std::max(X, 1));
     d2h(hw.data(), w, X * sizeof(double), s);
     int xk = 0;
-    if (g_dry || !(thr > 0)) xk = X;
+    if (g_dry) xk = g_kept.X > 0 ? std::min(g_kept.X, X) : X;
+    else if (!(thr > 0)) xk = X;
     else
         for (int q = 0; q < X; ++q) xk += hw[q] >= thr;
     out.X = xk; out.o = o; out.v = v;
@@ -1942,7 +1967,7 @@ static int naf_blocks(const Blocks& in, double thr, Blocks& out, Arena& ws, hipS
         if (cache) {
             k_copy(cache->N, N, (long long)X * X, s);
             k_copy(cache->w, w, X, s);
-            cache->valid = !g_dry;
+            cache->valid = !g_kept.bound;
         }
     }
     return naf_project(in, thr, N, w, out, ws, s);
@@ -2181,7 +2206,7 @@ static SolveOut solve_impl(Arena& ws, const double* eo, const double* ev, const 
         ws.release(mj);
     };
     // 4c-4e for every basis: its blocks in the kept natural orbitals, then the NAF truncation, the eigenproblems of the bases
-    // that drop virtuals as one batch (the others share one result; a dry run counts all of them in the batch)
+    // that drop virtuals as one batch (the others share one result; planning counts all of them in the batch)
     auto prep_all = [&](std::vector<Blocks>& Bn, std::vector<int>& xks) {
         GemmScratch gscr(ws, GEMM_SCRATCH);
         std::vector<Blocks> Bt(nb);
@@ -2190,7 +2215,7 @@ static SolveOut solve_impl(Arena& ws, const double* eo, const double* ev, const 
         for (int b = 0; b < nb; ++b) {
             if (vks[b] < 1) fail(ADC3_EINVAL, "SS-FNO threshold removes every virtual orbital");
             transform_blocks(B0, U_all + (long long)b * vv0, vks[b], Bt[b], ws, s);
-            if (naf > 0 && (g_dry || vks[b] != v)) {
+            if (naf > 0 && (g_kept.bound || vks[b] != v)) {
                 slot[b] = (int)own.size();
                 own.push_back(&Bt[b]);
             }
@@ -2204,7 +2229,7 @@ static SolveOut solve_impl(Arena& ws, const double* eo, const double* ev, const 
         for (int b = 0; b < nb; ++b) {
             Bn[b] = Bt[b];
             xks[b] = X;
-            if (g_dry && naf > 0) {
+            if (g_kept.bound && naf > 0) {
                 // the shared result is solved for here, after the projections of the bases before it
                 const size_t m1 = ws.mark();
                 double* N1 = take(ws, (long long)X * X);
@@ -3038,7 +3063,19 @@ static void plan_solve(int nocc, int nvir, int naux, int nroots, const adc3_opts
     (void)n;
     adc3_opts oc = op;
     oc.fno_keep_frac = 0.0;  // the canonical path's plan must not take the truncated route
-    if (path != 0) solve_impl(ws, dry_vec(), dry_vec(), B0, nroots, 1.0, 1.0, 1.0, op, nullptr);  // truncation path
+    if (path != 0) {
+        // Truncation path, kept counts not known yet.  An odd number of virtuals takes copies of the factor and of setup
+        // operands with even row strides, so a basis of v - 1 virtuals may need more than one of v: the plan is the larger
+        // of the two, and covers all below them (sizes within one parity grow with v; see KeptPlan for the others).
+        const long long v1 = nvir - 1;
+        for (int drop = 0; drop < 2; ++drop) {
+            if (drop && (v1 < 1 || nroots > v1 + (long long)nocc * v1 * v1)) continue;
+            KeptScope kept(drop ? nvir - 1 : 0, 0, true);
+            Arena w = ws;
+            solve_impl(w, dry_vec(), dry_vec(), B0, nroots, 1.0, 1.0, 1.0, op, nullptr);
+            ws.peak = std::max(ws.peak, w.peak);
+        }
+    }
     if (path != 1) {
         Arena ws2;
         ws2.used = 0;
@@ -3046,6 +3083,29 @@ static void plan_solve(int nocc, int nvir, int naux, int nroots, const adc3_opts
         ws.peak = std::max(ws.peak, ws2.peak + (size_t)(3 * naux * n * n * sizeof(double)));
     }
     g_dry = false;
+}
+
+extern "C" size_t adc3_debug_kept_workspace_bytes(int nocc, int nvir, int naux, int nroots, const adc3_opts* opts,
+                                                  int nvir_kept, int naux_kept, int naf) {
+    try {
+        check_dims(nocc, nvir, naux);
+        if (nvir_kept < 1 || nvir_kept > nvir || naux_kept < 0 || naux_kept > naux || nroots < 1) return 0;
+        adc3_opts op = resolve_opts(opts);
+        KeptScope kept(nvir_kept, naux_kept, false);
+        g_dry = true;
+        Arena ws;
+        Blocks B0;
+        B0.X = naux; B0.o = nocc; B0.v = nvir;
+        B0.Boo = take(ws, (long long)naux * nocc * nocc);
+        B0.Bov = take(ws, (long long)naux * nocc * nvir);
+        B0.Bvv = take(ws, (long long)naux * nvir * nvir);
+        solve_impl(ws, dry_vec(), dry_vec(), B0, nroots, 1.0, naf ? 1.0 : 0.0, 1.0, op, nullptr);
+        g_dry = false;
+        return ws.peak;
+    } catch (...) {
+        g_dry = false;
+        return 0;
+    }
 }
 
 extern "C" size_t adc3_ea_solve_workspace_bytes(int nocc, int nvir, int naux, int nroots, const adc3_opts* opts) {
