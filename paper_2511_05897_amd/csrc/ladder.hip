@@ -1186,12 +1186,15 @@ bool ladder_dual_tuned(const LadderTProb* p, int np, int M, int tm, int mtiles, 
         nch[i] = ladder_tuned_chunks(0, M, p[i].N, p[i].K, p[i].Z, p[i].K, p[i].G, p[i].ldg, C, p[i].N, partial, partial_elems,
                                      s);
     }
-    const std::string key = tune_key(0, M, n, n) + " one-launch";
+    // the row-major tiling, and the one launch's own rows per tile, tiles and K chunk; value 2: one launch, 1: two (the
+    // file keeps no values below 1)
+    const std::string key = tune_key(0, M, n, n) + " " + std::to_string(ladder_t_rows(M, mtiles)) + " " +
+                            std::to_string(mtiles) + " " + std::to_string(kc) + " launches";
     auto known = [&](bool& v) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         load_cache();
         auto it = g_tune.find(key);
-        if (it != g_tune.end()) v = it->second != 0;
+        if (it != g_tune.end()) v = it->second > 1;
         return it != g_tune.end();
     };
     bool one = true;
@@ -1223,11 +1226,15 @@ bool ladder_dual_tuned(const LadderTProb* p, int np, int M, int tm, int mtiles, 
             HIPCHK(hipEventElapsedTime(&ms, ev.e[0], ev.e[1]));
             if (round > 0) t[w] = std::min(t[w], ms);
         }
-    one = t[1] <= t[0];
+    // the row-major products were timed with their split-K sums; the one launch leaves its partial sums to the pass that
+    // reads the result, which streams them (3.5 TB/s) beyond the first chunk
+    long long part = 0;
+    for (int i = 0; i < np; ++i) part += ((p[0].K + kc - 1) / kc - 1) * (long long)M * p[i].N;
+    one = t[1] + 8.0f * (float)part / 3.5e9f <= t[0];
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_tune[key] = one;
-        store_cache(key, one);
+        g_tune[key] = one ? 2 : 1;
+        store_cache(key, one ? 2 : 1);
     }
     return one;
 }
