@@ -284,12 +284,14 @@ __global__ __launch_bounds__(NT) void abt_skinny_kernel(const double* __restrict
 //   part1[c][m][a] = sum over k in chunk c of r2[m][k] U[a][k]      (1p side, summed over chunks afterwards)
 //   out2[m][k]     = sum_a r1[m][a] U[a][k] + K0[k] r2[m][k]         (2p1h side with its zeroth-order diagonal
 //                                                                    K0 = e_a + e_b - e_i at k = (i,a,b))
-// for m < M <= 16.  A workgroup takes one K chunk; each 16-k slab of U is loaded once, as the MFMA
+// for m < M <= 16.  The 16-k slabs of U are dealt out in turn (workgroup b takes slabs b, b + grid, ..: the "chunk" of
+// its partial sums); each is loaded once, as the MFMA
 // fragments of the 1p product (waves split the 16-row tiles of a, as abt_skinny_kernel does), and
 // parked in LDS; the four waves then read the slab back in the transposed fragment layout (contraction
 // over a, MFMA steps of four a dealt out round-robin to the waves), the four partial 16 x 16 tiles are
 // summed in LDS in wave order and the slab's out2 columns written.  Rows and ks past the ends read as
-// zero.  VEC: 16-byte loads (aligned rows), else element loads.  U_z in FP32 (the reduced-precision sigma passes)
+// zero.  A full slab is loaded 16 bytes at a time whatever the rows' alignment (element-aligned vectors; a cut-off last
+// slab by elements).  U_z in FP32 (the reduced-precision sigma passes)
 // is widened to FP64 on load: the same fragments, and sums in FP64.  (Issuing the next slab's loads before this one's
 // products, with two register sets and so two workgroups a CU, was slower: 445 against 340 us at o=20 v=200, 5
 // vectors.)  FP64 with aligned rows takes couple_lds_kernel below.

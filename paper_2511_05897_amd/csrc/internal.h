@@ -291,7 +291,6 @@ void k_check_B(const double* B, int X, int n, double* flags, hipStream_t s);
 void k_z_to_x(const double* z, double* x, double* xt, long long nblk, int v, hipStream_t s);
 // acc += S(d) + sqrt3*A(d)
 void k_d_to_z_add(double* acc, const double* d, long long nblk, int v, hipStream_t s);
-// particle-hole terms: operands from z ([nv][o] blocks of v x v) as rows (n,a) x cols (j,d):
 // Stored ladder in pair-symmetric (a <= b) and pair-antisymmetric (a < b) blocks, each padded to a
 // leading dimension that is a multiple of 8 (sa_lp(v), sa_lm(v); the padding is zero).
 long long sa_lp(int v);

@@ -9,8 +9,9 @@
 //
 // Both are streams.  They replace thirteen launches of a pass (copies, pack, transposes, operand build, split-K
 // reductions, unpack, final sums); a small sigma is bound by its launches (a kernel in a dependent chain takes at least
-// 4.7 us), a large one saves the round trips of the intermediate forms.  Whole sigma, before and now: o=4 v=20 3 vectors
-// 93 -> 46 us, o=13 v=91 5 vectors 396 -> 267, o=20 v=200 5 vectors 4.57 -> 4.39 ms.
+// 4.7 us), a large one saves the round trips of the intermediate forms.  Whole sigma without and with
+// them: o=4 v=20 3 vectors 93 -> 46 us, o=13 v=91 5 vectors 396 -> 267, o=20 v=200 5 vectors 4.57 -> 4.39 ms (43 us, 251 us
+// and 4.1 ms since the ladder's tiles take 4-row strips).
 #include "internal.h"
 #include <algorithm>
 
@@ -27,8 +28,7 @@ __device__ inline long long qidx(int a, int b, int v) {  // a < b
 // A workgroup takes the tile pair (tc <= td) of 16 x 16 elements for 16 rows m = (n, j): 128-byte runs on every side
 // (along d and c of z, along c and d of the operands' columns, along m of the k-major packed rows).  16 waves a workgroup:
 // a small sigma has few tile pairs and waits for each (one vector of o=16 v=120, 37 workgroups: 26 us with four waves,
-// 9.3
-// with 16; five of o=20 v=200: 42 and 35).
+// 9.3 with 16; five of o=20 v=200: 42 and 35).
 constexpr int PT = 16, PR = 17, PM = PT * PR + 1;  // tile, LDS row stride, stride between rows m
 
 struct SigmaPrep {
