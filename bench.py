@@ -74,16 +74,19 @@ def parse():
     return ap.parse_args()
 
 
-# HBM traffic of the ladder kernel per launch, from two rocprofv3 --pmc runs (FETCH_SIZE,
+# HBM traffic of the ladder's two kernels per launch (both pair blocks), from two rocprofv3 --pmc runs (FETCH_SIZE,
 # then WRITE_SIZE) of `bench.py --sigma-only`, each scaled by the same counter's reading
-# for a copy of known size.  Keyed by a hash of the kernel's source and of the pair-block packing
-# that sets its launch shapes: a change to either reports null until it is measured again.
+# for a copy of known size.  bytes_per_launch is the 100-row launch's; a solve's launches of up to 20 rows read half of
+# each pair block instead (few_rows).  Keyed by a hash of the kernels' sources and of the pair-block packing
+# that sets their launch shapes: a change to any reports null until it is measured again.
 LADDER_TRAFFIC = {
-    "540b91534ad136e7": {
-        "bytes_per_launch": 7.185e9, "read_bytes": 7.056e9, "written_bytes": 0.129e9,
+    "24c9d86dd26d31b0": {
+        "bytes_per_launch": 7.188e9, "read_bytes": 7.059e9, "written_bytes": 0.129e9,
         "fetch_scale": 2.0, "write_scale": 1.0,
         "measured_on": "sigma ladder o=20 v=200 X=128, 5 vectors (M=100, ladder_f64t_kernel), both pair blocks in one launch, "
                        "2 K-chunks",
+        "few_rows": {"bytes_per_launch": 4.078e9, "read_bytes": 3.795e9, "written_bytes": 0.283e9,
+                     "measured_on": "the same, 1 vector (M=20, ladder_sym_kernel and the launch that adds its partial sums)"},
         "profile": "profiles/sigma_o20v200x128_kernels.md"},
 }
 
@@ -127,11 +130,11 @@ def min_factor(X, v, o, nv_max=16):
 
 
 def ladder_traffic():
-    """The ladder kernel's source and the pair-block packing that sets its launch shapes, hashed together."""
+    """The ladder kernels' sources and the pair-block packing that sets their launch shapes, hashed together."""
     import hashlib
     d = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2511_05897_amd", "csrc")
     h = hashlib.sha256()
-    for f in ("ladder.hip", "ladder_sa.hip"):
+    for f in ("ladder.hip", "ladder_sa.hip", "ladder_sym.hip"):
         h.update(open(os.path.join(d, f), "rb").read())
     h = h.hexdigest()[:16]
     return h, LADDER_TRAFFIC.get(h)
@@ -558,15 +561,17 @@ def main():
         ctx = adc.Context(d(e2), d(v2), d(B2), 3, nroots=0, precision=a.sigma_precision)
         r = torch.randn((5, ctx.N), dtype=torch.float64, device="cuda")
         out = torch.empty_like(r)
-        for _ in range(a.sigma_reps):
-            ctx.sigma(r, out, precision=a.sigma_precision)
+        for nv in (5, 1):  # 100 rows of the ladder (ladder_f64t_kernel), then 20 (ladder_sym_kernel)
+            for _ in range(a.sigma_reps):
+                ctx.sigma(r[:nv], out[:nv], precision=a.sigma_precision)
         torch.cuda.synchronize()
         # plain copy of known size: 2 GiB read + 2 GiB written
         x = torch.empty(1 << 28, dtype=torch.float64, device="cuda").fill_(1.0)
         y = torch.empty_like(x)
         y.copy_(x)
         torch.cuda.synchronize()
-        print(json.dumps({"mode": "sigma-only", "sigma_calls": a.sigma_reps, "nvec": 5, "precision": a.sigma_precision,
+        print(json.dumps({"mode": "sigma-only", "sigma_calls": a.sigma_reps, "nvec": [5, 1],
+                          "precision": a.sigma_precision,
                           "ladder_flops_per_launch": 2.0 * 100 * 200 ** 4, "copy_bytes_each_way": 8 << 28}))
         return
     if a.dfladder_only:
@@ -869,6 +874,8 @@ def main():
                      "achieved": rf["achieved"], "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
                      "frac": rf["achieved"] / PEAK_FP64_TFLOPS,
                      "traffic": traffic["bytes_per_launch"] if traffic else None,
+                     "traffic_of": "a launch of 100 rows (ladder_f64t_kernel); launches of up to 20 rows: "
+                                   "traffic_detail.few_rows",
                      "traffic_detail": traffic, "kernel_source_hash": src_hash,
                      "bound_time_frac": rf["bound_time_frac"],
                      "launches": rf["launches"], "avg_launch_ms": rf["avg_launch_ms"],
