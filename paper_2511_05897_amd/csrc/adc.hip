@@ -652,13 +652,13 @@ static void sigma_pass(Ctx* c, Arena& ws, const double* rr, double* ss, int nv, 
         const bool km64 = stored && prec == 0 && (rows3 || lp < LADDER_STREAM_MIN);
         double* W = stored ? take(ws, ((long long)M + 3) * (lp + lm)) : nullptr;
         double* CW = stored ? take(ws, (long long)M * (lp + lm)) : nullptr;
-        bool dual = km64 && ladder_t_shape(M, lp, lm, ldt8, pe, tm, mt, kc);
+        bool dual = !g_dry && km64 && ladder_t_shape(M, lp, lm, ldt8, pe, tm, mt, kc);  // (no size depends on it)
         LadderTProb pr[2];
         if (dual) {
             const long long nch = (lp + kc - 1) / kc;
             pr[0] = LadderTProb{(int)lp, (int)lp, W, ldt8, c->G, lp, pbuf};
             pr[1] = LadderTProb{(int)lm, (int)lm, W + ldt8 * lp, ldt8, c->Gm, lm, pbuf + nch * M * lp};
-            if (!g_dry && !rows3 && !ladder_dual_tuned(pr, lm > 0 ? 2 : 1, M, tm, mt, kc, CW, pbuf, pe, s))
+            if (!rows3 && !ladder_dual_tuned(pr, lm > 0 ? 2 : 1, M, tm, mt, kc, CW, pbuf, pe, s))
                 dual = false;
         }
         // up to 20 rows of streamed blocks: half of each symmetric G is read (whole sigma,
@@ -696,7 +696,7 @@ static void sigma_pass(Ctx* c, Arena& ws, const double* rr, double* ss, int nv, 
                 df_ladder(0, M, v, X, c->Bvv, c->zb, c->sb, false, V, ve, s);
             }
             ws.release(mk);
-        } else if (dual && !g_dry && ladder_t_supported(M, (int)lp, (int)lp, W, ldt, c->G, lp)) {
+        } else if (dual && ladder_t_supported(M, (int)lp, (int)lp, W, ldt, c->G, lp)) {
             // both pair blocks in one launch, their partial sums read by k_sigma_fin
             const double fl = 2.0 * M * ((double)lp * lp + (double)lm * lm);
             const double by = 8.0 * ((double)lp * lp + (double)lm * lm) + 16.0 * M * (double)(lp + lm);
@@ -2487,7 +2487,7 @@ static SolveOut solve_impl(Arena& ws, const double* eo, const double* ev, const 
             // only the roots up to the highest matched one of this basis are needed
             int mmax = 0;
             for (int k : ks) mmax = std::max(mmax, match[k]);
-            const int nr3 = std::min(nroots, mmax + 1);
+            const int nr3 = g_dry ? nroots : std::min(nroots, mmax + 1);  // (counted for any match)
             double* X3 = take(ar, (long long)nr3 * Nk);
             DavResult a3 = davidson_impl(c3, ar, nr3, conv, op.max_iter, op.max_subspace, X3, st, op.precision,
                                          op.precond == 1, nullptr, Y2k, nroots, level >= 3 ? pm3 : pm2);
@@ -2555,6 +2555,7 @@ static SolveOut solve_impl(Arena& ws, const double* eo, const double* ev, const 
             const bool cb = run_basis(b, Bn, xk, ws, s);
             out.all_conv = out.all_conv && cb;
             ws.release(mark);
+            if (g_dry) break;  // the others take the same
         }
     } else if (engine == 2) {
         // every basis's blocks first, on the caller's stream; then each basis's solves on a host thread and a
@@ -2564,13 +2565,18 @@ static SolveOut solve_impl(Arena& ws, const double* eo, const double* ev, const 
         std::vector<int> xks(nb, X);
         prep_all(Bn, xks);
         std::vector<Arena> sub(nb);
+        std::map<std::pair<int, int>, size_t> need;  // by kept virtuals and auxiliary functions
         for (int b = 0; b < nb; ++b) {
-            const bool was = g_dry;
-            g_dry = true;
-            Arena count;
-            run_basis(b, Bn[b], xks[b], count, nullptr);
-            g_dry = was;
-            const size_t bytes = (count.peak + 4096 + 255) / 256 * 256;
+            size_t& peak = need[{vks[b], xks[b]}];
+            if (peak == 0) {
+                const bool was = g_dry;
+                g_dry = true;
+                Arena count;
+                run_basis(b, Bn[b], xks[b], count, nullptr);
+                g_dry = was;
+                peak = count.peak;
+            }
+            const size_t bytes = (peak + 4096 + 255) / 256 * 256;
             sub[b].base = ws.take<char>(bytes);
             sub[b].cap = bytes;
         }
