@@ -272,7 +272,8 @@ __global__ void offnorm_part_kernel(const double* A, int n, double* part, const 
 // nrm[2b] is kept from check to check: a matrix within 100 times the threshold whose off-diagonal norm did not halve
 // since the last check is at its rounding floor and done as well.  Slow convergence further up is no floor: with a large
 // cluster of eigenvalues the off-diagonal norm falls linearly from about 1e-24 of the total on (a 150-fold eigenvalue at
-// n = 200; ended there, the residual is 8e-13 of the norm, here 7e-15).
+// n = 200; ended there, the residual is 6e-13 of the norm, here 8e-16).  The metric matrices of the NAF step, whose
+// eigenvalues fall off fast, do the same (from 1e-22 on at n = 201) and take two more sweeps of eleven for it.
 __global__ __launch_bounds__(64) void offnorm_sum_kernel(const double* part, int n, double* nrm, int* active) {
     const int bm = blockIdx.x;
     if (!active[bm]) return;
