@@ -580,9 +580,10 @@ __global__ __launch_bounds__(1024) void bj_rayleigh_kernel(const double* A0, con
 // n = 600 (14 at n = 200), which an eigenvector pair shows divided by its gap.  One first-order correction from the
 // input matrix takes that out:  x_j += sum_i E_ij x_i  with, for r = I - V^T V and the residuals q_j = A0 x_j - w_j x_j,
 //   E_ij = x_i . q_j / (w_j - w_i),   E_ji = r_ij - E_ij,   E_ii = r_ii / 2,
-// and E_ij = E_ji = r_ij / 2 (orthogonality alone) for a pair whose rotation would exceed 2^-26, where the neglected square
-// is no longer below the rounding: clusters, whose vectors are any basis of their space.  Both elements of a pair come
-// from one workgroup and one decision, so the correction is antisymmetric up to r.
+// and E_ij = E_ji = r_ij / 2 (orthogonality alone) for a pair whose rotation would exceed 2^-18: close clusters, whose
+// vectors are any basis of their space.  Both elements of a pair come from one workgroup and one decision, so the
+// correction is antisymmetric up to r; applied as E + E^2 / 2 + E^3 / 6 it is orthogonal to the rounding, which loose clusters
+// need (400 eigenvalues within 1e-8: V^T V - I 3e-13 with E alone, where the rotations leave 1e-13).
 // grid (nt (nt + 1) / 2, batch), 256 threads: the 16 x 16 tile pair (i tile <= j tile), K dealt to the waves; E[i][j].
 __global__ __launch_bounds__(256) void bj_correct_kernel(const double* Vt, const double* W, const double* w, int n, double* E) {
     const long long o = (long long)blockIdx.y * n * n;
@@ -618,15 +619,17 @@ __global__ __launch_bounds__(256) void bj_correct_kernel(const double* Vt, const
     if (x > y || y >= n) return;
     const double gs = ((sg[0][t] + sg[1][t]) + sg[2][t]) + sg[3][t], qs = ((sq[0][t] + sq[1][t]) + sq[2][t]) + sq[3][t];
     const double gap = wb[y] - wb[x], r = (x == y ? 1.0 : 0.0) - gs;
-    const bool rot = x != y && fabs(qs) <= 0x1p-26 * fabs(gap);
+    const bool rot = x != y && fabs(qs) <= 0x1p-18 * fabs(gap);
     const double exy = rot && gap != 0.0 ? qs / gap : 0.5 * r;
     E[o + (long long)x * n + y] = exy;
     if (x != y) E[o + (long long)y * n + x] = r - exy;
 }
 
-// V[k][j] = Vt[j][k] + sum_i E[i][j] Vt[i][k]: grid (nt, nt, batch), 256 threads, a 16 x 16 tile (j, k), i dealt to the
-// waves; written transposed (vectors as columns) through LDS.
-__global__ __launch_bounds__(256) void bj_update_kernel(const double* Vt, const double* E, int n, double* V) {
+// Out[j][k] = Vt[j][k] + f sum_i E[i][j] T[i][k], or as Out[k][j] (COLS: vectors as columns): grid (nt, nt, batch), 256
+// threads, a 16 x 16 tile (j, k), i dealt to the waves; through LDS, so that lanes run along Out's rows.
+template <bool COLS>
+__global__ __launch_bounds__(256) void bj_update_kernel(const double* Vt, const double* E, const double* T, double f, int n,
+                                                        double* Out) {
     const long long o = (long long)blockIdx.z * n * n;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 15, lk = lane >> 4;
     const int j0 = blockIdx.x * 16, k0 = blockIdx.y * 16, j = j0 + lr, k = k0 + lr;
@@ -636,7 +639,7 @@ __global__ __launch_bounds__(256) void bj_update_kernel(const double* Vt, const 
         for (int s = 0; s < 4; ++s) {
             const int i = i0 + 4 * s + lk;
             const double a = (i < n && j < n) ? E[o + (long long)i * n + j] : 0.0;
-            const double b = (i < n && k < n) ? Vt[o + (long long)i * n + k] : 0.0;
+            const double b = (i < n && k < n) ? T[o + (long long)i * n + k] : 0.0;
             d = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, d, 0, 0, 0);
         }
     __shared__ double sd[4][16][17];
@@ -646,8 +649,10 @@ __global__ __launch_bounds__(256) void bj_update_kernel(const double* Vt, const 
     const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
     vt[r][c] = (j0 + r < n && k0 + c < n) ? Vt[o + (long long)(j0 + r) * n + k0 + c] : 0.0;
     __syncthreads();
-    if (k0 + r < n && j0 + c < n)
-        V[o + (long long)(k0 + r) * n + j0 + c] = vt[c][r] + (((sd[0][c][r] + sd[1][c][r]) + sd[2][c][r]) + sd[3][c][r]);
+    const int x = COLS ? c : r, y = COLS ? r : c;  // element (j0 + x, k0 + y)
+    if (j0 + x >= n || k0 + y >= n) return;
+    Out[o + (COLS ? (long long)(k0 + y) * n + j0 + x : (long long)(j0 + x) * n + k0 + y)] =
+        vt[x][y] + f * (((sd[0][x][y] + sd[1][x][y]) + sd[2][x][y]) + sd[3][x][y]);
 }
 }  // namespace
 
@@ -745,11 +750,15 @@ void eig_block(double* A, int n, int nb, double* w, double* V, double* scratch, 
         }
         LAUNCHCHK();
     }
-    // A is free from here on (it takes Vt A0), and A0 after the quotients (it takes the correction)
+    // A is free from here on (it takes Vt A0), and A0 after the quotients (it takes the correction E):
+    // V = Vt + E^T (Vt + E^T (Vt + E^T Vt / 3) / 2), by way of V and A
     const int nt = (n + 15) / 16;
     hipLaunchKernelGGL(bj_rayleigh_kernel, dim3(nt, nb), dim3(1024), 0, s, A0, Vt, n, w, A);
     hipLaunchKernelGGL(bj_correct_kernel, dim3(nt * (nt + 1) / 2, nb), dim3(256), 0, s, Vt, A, w, n, A0);
-    hipLaunchKernelGGL(bj_update_kernel, dim3(nt, nt, nb), dim3(256), 0, s, Vt, A0, n, V);
+    const dim3 gu(nt, nt, nb);
+    hipLaunchKernelGGL(bj_update_kernel<false>, gu, dim3(256), 0, s, Vt, A0, Vt, 1.0 / 3.0, n, V);
+    hipLaunchKernelGGL(bj_update_kernel<false>, gu, dim3(256), 0, s, Vt, A0, V, 0.5, n, A);
+    hipLaunchKernelGGL(bj_update_kernel<true>, gu, dim3(256), 0, s, Vt, A0, A, 1.0, n, V);
     LAUNCHCHK();
 }
 }  // namespace
